@@ -153,6 +153,21 @@ __device__ __forceinline__ float col4_sum(float v) {
   pair_xor32(v, a, b);
   return a + b;
 }
+// Max with the lowest index among equal values, over lanes l, l ^ 16, l ^ 32,
+// l ^ 48.
+__device__ __forceinline__ void col4_argmax(float& v, int& idx) {
+  float a, b, ia, ib;
+  pair_xor16(v, a, b);
+  pair_xor16(__int_as_float(idx), ia, ib);
+  bool second = b > a || (b == a && __float_as_int(ib) < __float_as_int(ia));
+  v = second ? b : a;
+  idx = __float_as_int(second ? ib : ia);
+  pair_xor32(v, a, b);
+  pair_xor32(__int_as_float(idx), ia, ib);
+  second = b > a || (b == a && __float_as_int(ib) < __float_as_int(ia));
+  v = second ? b : a;
+  idx = __float_as_int(second ? ib : ia);
+}
 // Max with the lowest index among equal values, over the 16 lanes of each row.
 template <int CTRL>
 __device__ __forceinline__ void argmax_step(float& v, int& idx) {
@@ -204,6 +219,12 @@ __device__ __forceinline__ void st_coherent_bf2(bf16* p, float a, float b) {  //
   const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, f2bf(b));
   __hip_atomic_store((LLMCAD_GLOBAL uint32_t*)p, lo | (hi << 16), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_coherent_bf4(bf16* p, f32x4 v) {  // p 8-byte aligned
+  uint64_t bits = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) bits |= (uint64_t)__builtin_bit_cast(uint16_t, f2bf(v[i])) << (16 * i);
+  __hip_atomic_store((LLMCAD_GLOBAL uint64_t*)p, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_coherent_bf(bf16* p, float a) {  // p 2-byte aligned
   __hip_atomic_store((LLMCAD_GLOBAL uint16_t*)p, __builtin_bit_cast(uint16_t, f2bf(a)), __ATOMIC_RELAXED,

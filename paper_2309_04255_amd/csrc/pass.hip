@@ -535,7 +535,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(ba[u][rb], b[c], acc[rb][c]);
+        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(b[c], ba[u][rb], acc[rb][c]);
       __builtin_amdgcn_sched_barrier(0);
       load_a(u, i + u + D);
     }
@@ -547,7 +547,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(ba[u][rb], bw[u][c], acc[rb][c]);
+        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(bw[u][c], ba[u][rb], acc[rb][c]);
       __builtin_amdgcn_sched_barrier(0);
       load_w(u, i + u + D, true);
       load_a(u, i + u + D);
@@ -562,7 +562,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb)
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(ba[u][rb], bw[u][c], acc[rb][c]);
+        for (int c = 0; c < C; ++c) acc[rb][c] = mfma16x16x32(bw[u][c], ba[u][rb], acc[rb][c]);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -714,7 +714,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
     for (int c = 0; c < C; ++c) {
       const bf16x8 b = lds_ld<bf16x8>(buf + (size_t)c * 1024 + lane * 16);
 #pragma unroll
-      for (int r = 0; r < RB; ++r) acc[r][c] = mfma16x16x32(ba[u][r], b, acc[r][c]);
+      for (int r = 0; r < RB; ++r) acc[r][c] = mfma16x16x32(b, ba[u][r], acc[r][c]);
     }
     if (refill) {
       load_w(u, i + D);
@@ -797,6 +797,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
                                                                           int nb0, int wait_phase, char* lds,
                                                                           GemmLds& gl, int* lds_flag) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
@@ -810,7 +811,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   // this wave's groups: wave + 4 i
   const u32x4* wt = (const u32x4*)io.w + ((size_t)nb0 * gs + wave) * 64 + lane;
   const size_t cstride = (size_t)gs * 64;
-  const uint16_t* st = io.sc + ((size_t)nb0 * gs + wave) * kNB + (lane & 15);
+  const uint16_t* st = io.sc + ((size_t)nb0 * gs + wave) * kNB + 4 * (lane >> 4);  // (this lane's four columns)
   const size_t sstride = (size_t)gs * kNB;
   const bf16x8* at = io.a + (size_t)wave * 4 * MB * 64 + lane;
   const u32x4* zero_w = (const u32x4*)p.zero + lane;
@@ -818,7 +819,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
   const f32x4* zero4 = (const f32x4*)p.zero + lane;
   u32x4 bw[D][C];
-  uint32_t bs[D][C];
+  u32x2 bs[D][C];
   bf16x8 ba[D][4][MB];
   auto load_w = [&](int slot, int i) {  // group i of this wave, or the zero line past the last
     const bool live = i < ns;
@@ -826,7 +827,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
     for (int c = 0; c < C; ++c) {
       bw[slot][c] = __builtin_nontemporal_load(
           (const LLMCAD_GLOBAL u32x4*)opaque(live ? wt + c * cstride + (size_t)(kWaves * i) * 64 : zero_w));
-      bs[slot][c] = ldg(opaque(live ? st + c * sstride + (size_t)(kWaves * i) * kNB : zero_s));
+      bs[slot][c] = ldg((const u32x2*)opaque(live ? st + c * sstride + (size_t)(kWaves * i) * kNB : zero_s));
     }
   };
   auto load_a = [&](int slot, int i) {
@@ -923,13 +924,15 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) tmp[rb][c] = mfma16x16x32(ba[u][t][rb], b[c], tmp[rb][c]);
-        corr[rb] = mfma16x16x32(ba[u][t][rb], c136, corr[rb]);
+        for (int c = 0; c < C; ++c) tmp[rb][c] = mfma16x16x32(b[c], ba[u][t][rb], tmp[rb][c]);
+        corr[rb] = mfma16x16x32(c136, ba[u][t][rb], corr[rb]);
       }
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      const float sc = __uint_as_float((bs[u][c] & 0xFFFFu) << 16);  // the column's bf16 scale
+      // the four columns' bf16 scales
+      const f32x4 sc = {__uint_as_float(bs[u][c][0] << 16), __uint_as_float(bs[u][c][0] & 0xFFFF0000u),
+                        __uint_as_float(bs[u][c][1] << 16), __uint_as_float(bs[u][c][1] & 0xFFFF0000u)};
 #pragma unroll
       for (int rb = 0; rb < MB; ++rb) acc[rb][c] += sc * (tmp[rb][c] - corr[rb]);
     }
@@ -1052,109 +1055,136 @@ __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io, GemmLds
 // Epilogue of one accumulator tile ("unit": block c of the tile x row block
 // rb, 16 x 16).  The unit's sum is the nsum partial tiles in LDS added in
 // order (the four waves' partials, or a split-K group's partial sums in
-// slice order); lane l holds rows 16 rb + 4 (l / 16) + i, i < 4, column
-// l % 16.
+// slice order).  The products take the weights as their first operand, so
+// lane l holds row 16 rb + l % 16, columns 4 (l / 16) + i, i < 4: four
+// consecutive columns of one row, which every output stores in one piece
+// (8 bytes of bf16, 16 of fp32) and whose partners of the rotary embedding
+// and of the SwiGLU pair (8 columns on) sit 32 lanes on.  (The other operand
+// order gives a lane four rows of one column: four times the stores, of 2 to
+// 8 bytes.  At the 7B shape and 128 rows the QKV and gate/up epilogues took
+// 7.0 and 7.7 us that way, 5.3 and 6.3 us this way; 2.7 and 3.0 against 2.2
+// and 2.6 us at 31 nodes.)
 // Outputs are written with device-coherent stores.
 template <int MB, int EPI>
 __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, const char* lds, int cw, int c, int rb,
                                               int nb, GemmLds& gl, int nsum) {
-  const int lane = threadIdx.x & 63, j = lane & 15, q4 = lane >> 4;
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int unit = c * MB + rb;
-  f32x4 s = lds_ld<f32x4>(lds + tw_off() + ((size_t)unit * 64 + lane) * 16);
+  f32x4 v = lds_ld<f32x4>(lds + tw_off() + ((size_t)unit * 64 + lane) * 16);
 #pragma unroll
   for (int w = 1; w < kWaves; ++w)
-    if (w < nsum) s += lds_ld<f32x4>(lds + tw_off() + ((size_t)(w * cw * MB + unit) * 64 + lane) * 16);
-  float v[4] = {s[0], s[1], s[2], s[3]};
-  const int rr0 = 4 * q4;  // first row of this lane inside the row block
-  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) {  // the norm's per-row scale
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] *= gl.rstd[16 * rb + rr0 + i];
-  }
+    if (w < nsum) v += lds_ld<f32x4>(lds + tw_off() + ((size_t)(w * cw * MB + unit) * 64 + lane) * 16);
+  const int r = 16 * rb + li;
+  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) v *= gl.rstd[r];  // the norm's per-row scale
   const char* epi = lds + epi_off(cw, MB, nsum);
-  const int col = kNB * nb + j;
+  const int col = kNB * nb + 4 * g;
   if constexpr (EPI == EPI_QKV) {
     const int d = p.d, dh = p.Dh;
     if (kNB * nb < 2 * d) {
-      // q or k: this block holds dims [8t, 8t+8) (lanes j < 8) and their
-      // rotary partners + Dh/2 (lanes j >= 8) of one head.
+      // q or k: this block holds dims [8t, 8t+8) (lanes < 32) and their
+      // rotary partners + Dh/2 (lanes >= 32) of one head.
       const int part = (kNB * nb) / d, cq = (kNB * nb) % d, hh = cq / dh, t = (cq % dh) / kNB;
-      const int dim = 8 * t + (j & 7) + (j < 8 ? 0 : dh / 2);
-      bf16* base = part == 0 ? io.q + hh * dh : io.kc + (size_t)hh * p.cap * dh;
-      const char* csu = epi + (size_t)unit * 1024;
+      const int dim = 8 * t + 4 * (g & 1) + (g < 2 ? 0 : dh / 2);
+      const char* csu = epi + (size_t)unit * 1024 + (size_t)(li * 8 + 4 * (g & 1)) * 8;
+      const f32x4 cs01 = lds_ld<f32x4>(csu), cs23 = lds_ld<f32x4>(csu + 16);
+      const float cs[4] = {cs01[0], cs01[2], cs23[0], cs23[2]}, sn[4] = {cs01[1], cs01[3], cs23[1], cs23[3]};
+      f32x4 o;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int rr = rr0 + i, r = 16 * rb + rr;
-        const float2 cs = lds_ld<float2>(csu + (size_t)(rr * 8 + (j & 7)) * 8);
-        const float partner = dpp_f<kDppRowRor8>(v[i]);
-        const float outv = j < 8 ? v[i] * cs.x - partner * cs.y : v[i] * cs.x + partner * cs.y;
-        const float nxt = dpp_f<kDppRowShl1>(outv);
-        if (r < p.n && (j & 1) == 0) {
-          bf16* dst = part == 0 ? base + (size_t)r * d : base + (size_t)(p.prefix_len + p.m0 + r) * dh;
-          st_coherent_bf2(dst + dim, outv, nxt);
-        }
+        float lo, hi;
+        pair_xor32(v[i], lo, hi);
+        o[i] = g < 2 ? lo * cs[i] - hi * sn[i] : hi * cs[i] + lo * sn[i];
+      }
+      if (r < p.n) {
+        bf16* dst = part == 0 ? io.q + hh * dh + (size_t)r * d
+                              : io.kc + ((size_t)hh * p.cap + p.prefix_len + p.m0 + r) * dh;
+        st_coherent_bf4(dst + dim, o);
       }
     } else {
-      // v: the cache holds V transposed per head ([Dh][cap]); this lane's
-      // four rows are four consecutive slots of one dim
+      // v: the cache holds V transposed per head ([Dh][cap]); the 16 lanes of
+      // a quarter wave hold 16 consecutive slots of each of its four dims
       const int cv = col - 2 * d, hh = cv / dh, dim = cv % dh;
-      bf16* vrow = io.vc + ((size_t)hh * dh + dim) * p.cap + p.prefix_len + p.m0;
+      bf16* vcol = io.vc + ((size_t)hh * dh + dim) * p.cap + p.prefix_len + p.m0 + r;
+      if (r < p.n) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 16 * rb + rr0 + i;
-        if (r < p.n) st_coherent_bf(vrow + r, v[i]);
+        for (int i = 0; i < 4; ++i) st_coherent_bf(vcol + (size_t)i * p.cap, v[i]);
       }
     }
   } else if constexpr (EPI == EPI_RESID) {
-    const char* xu = epi + (size_t)unit * 1024;
-    const float g = bf2f(lds_ld<bf16>(epi + (size_t)(cw * MB + c) * 1024 + 16 * (j >> 3) + 2 * (j & 7)));
+    const f32x4 xin = lds_ld<f32x4>(epi + (size_t)unit * 1024 + (size_t)(li * 16 + 4 * g) * 4);
+    const bf16x4 gn = lds_ld<bf16x4>(epi + (size_t)(cw * MB + c) * 1024 + 8 * g);
+    f32x4 xn = xin + v, xg;
+    float sq = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int rr = rr0 + i, r = 16 * rb + rr;
-      const float xn = r < p.n ? lds_ld<float>(xu + (size_t)(rr * 16 + j) * 4) + v[i] : 0.0f;
-      const float xn1 = dpp_f<kDppRowShl1>(xn);
-      if (r < p.n && (j & 1) == 0) st_coherent2(io.x_out + (size_t)r * p.d + col, xn, xn1);
-      const float xg = xn * g;
-      const float xg1 = dpp_f<kDppRowShl1>(xg);
-      if (r < p.n && (j & 1) == 0) st_coherent_bf2(io.xg_out + frag_off(r, col, MB), xg, xg1);
-      const float sq = row16_sum(xn * xn);  // sum of squares over the block's 16 columns
-      if (j == 0 && r < p.n) st_coherent(io.ssq_out + (size_t)nb * p.Mp + r, sq);
+      xg[i] = xn[i] * bf2f(gn[i]);
+      sq += xn[i] * xn[i];
+    }
+    sq = col4_sum(sq);  // sum of squares over the block's 16 columns
+    if (r < p.n) {
+      float* dst = io.x_out + (size_t)r * p.d + col;
+      st_coherent2(dst, xn[0], xn[1]);
+      st_coherent2(dst + 2, xn[2], xn[3]);
+      st_coherent_bf4(io.xg_out + frag_off(r, col, MB), xg);
+      if (g == 0) st_coherent(io.ssq_out + (size_t)nb * p.Mp + r, sq);
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
-    const int f = 8 * nb + (j & 7);
+    f32x4 hv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int r = 16 * rb + rr0 + i;
-      const float up = dpp_f<kDppRowRor8>(v[i]);
-      const float hv = v[i] / (1.0f + expf(-v[i])) * up;
-      const float nxt = dpp_f<kDppRowShl1>(hv);
-      if (r < p.n && j < 8 && (j & 1) == 0) st_coherent_bf2(io.h + frag_off(r, f, MB), hv, nxt);
+      float gate, up;
+      pair_xor32(v[i], gate, up);
+      hv[i] = gate / (1.0f + expf(-gate)) * up;
     }
+    if (r < p.n && g < 2) st_coherent_bf4(io.h + frag_off(r, 8 * nb + 4 * g, MB), hv);
   } else {  // EPI_LOGITS
-    const bool vcol = col < p.V;
     // (with candidate summaries the end of the pass reads the stored rows
     // back: device-coherent stores)
     const bool summ = p.cand != nullptr;
+    if (p.logits != nullptr && r < p.n && r >= p.row_lo) {
+      float* dst = p.logits + (size_t)(r - p.row_lo) * p.V + col;
+      // four columns in one piece where every row of the caller's buffer allows it
+      if ((((uintptr_t)p.logits | (uintptr_t)p.V * 4) & 15) == 0) {
+        if (col < p.V) {  // (V is then a multiple of 4)
+          if (summ) {
+            st_coherent2(dst, v[0], v[1]);
+            st_coherent2(dst + 2, v[2], v[3]);
+          } else {
+            stg((f32x4*)dst, v);
+          }
+        }
+      } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * rb + rr0 + i;
-      const bool valid = vcol && r < p.n;
-      if (valid && p.logits != nullptr && r >= p.row_lo) {
-        float* dst = p.logits + (size_t)(r - p.row_lo) * p.V + col;
-        if (summ)
-          st_coherent(dst, v[i]);
-        else
-          stg(dst, v[i]);
+        for (int i = 0; i < 4; ++i)
+          if (col + i < p.V) {
+            if (summ)
+              st_coherent(dst + i, v[i]);
+            else
+              stg(dst + i, v[i]);
+          }
       }
-      float mv = valid ? v[i] : -INFINITY;
-      int mi = valid ? col : 0x7fffffff;
-      row16_argmax(mv, mi);  // argmax over the block's 16 columns
-      // the block's sum of exp(logit - its max), for the softmax normaliser
-      const float se = summ ? row16_sum(valid ? expf(v[i] - mv) : 0.0f) : 0.0f;
-      if (j == 0) {
-        gl.red_v[r][c] = mv;
-        gl.red_i[r][c] = mi;
-        gl.red_s[r][c] = se;
+    }
+    // argmax over the block's 16 columns (lowest index among equal values)
+    float mv = -INFINITY;
+    int mi = 0x7fffffff;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (col + i < p.V && r < p.n && (v[i] > mv || (v[i] == mv && col + i < mi))) {
+        mv = v[i];
+        mi = col + i;
       }
+    col4_argmax(mv, mi);
+    // the block's sum of exp(logit - its max), for the softmax normaliser
+    float se = 0.0f;
+    if (summ) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) se += col + i < p.V && r < p.n ? expf(v[i] - mv) : 0.0f;
+      se = col4_sum(se);
+    }
+    if (g == 0) {
+      gl.red_v[r][c] = mv;
+      gl.red_i[r][c] = mi;
+      gl.red_s[r][c] = se;
     }
   }
 }

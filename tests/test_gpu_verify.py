@@ -323,6 +323,39 @@ def test_prefill_last_logits(model):
     parity.check_logits(out.cpu().numpy()[None], ref[-1:], "prefill")
 
 
+@pytest.mark.parametrize("vocab", [1003, 1006, 1020, 1024])
+def test_logit_columns(vocab):
+    # The LM head's epilogue stores four columns of a row in one piece where
+    # the vocabulary and the caller's buffer allow it (1020: a ragged last
+    # block of whole pieces) and one by one elsewhere (odd and even
+    # vocabularies; a buffer off 16-byte alignment): the same bits either way,
+    # the oracle bar, and the lowest index of the row's maximum as its token.
+    binding = _gpu()
+    shape = workloads.ModelShape("logits", 2, 256, 4, 64, 688, vocab, seed=0x5EED0001)
+    gen = workloads.make_weights(shape, "cuda")
+    sess = binding.Session(shape, capacity=64, max_n=32)
+    sess.load_weights(gen)
+    parent = TREES["random_n20"]
+    n = len(parent)
+    tok = workloads.draw_tokens(n, vocab, seed=29)
+    sess.verify_tree(0, tok, parent)
+    logits = sess.results(n)[0].numpy()
+    none = np.zeros((shape.n_layers, 0, shape.n_heads, shape.head_dim))
+    ref, _, _ = oracle.tree_forward(oracle_weights(shape), none, none, tok, parent, rounding=True)
+    parity.check_logits(logits, ref, f"V={vocab}")
+    off, _ = binding.workspace_region(sess.cfg, n, 4)
+    amax = sess.workspace[off:off + 4 * n].view(torch.int32).cpu().numpy()
+    np.testing.assert_array_equal(amax, np.argmax(logits, axis=1))
+    for shift in (1, 2):
+        buf = torch.full((n * vocab + 8,), float("nan"), dtype=torch.float32, device="cuda")
+        out = buf[shift:shift + n * vocab]
+        binding.verify_tree(sess.cfg, sess.packed, sess.k_cache, sess.v_cache, 0, tok, parent, out, sess.path,
+                            sess.accept_len, sess.next_token, sess.workspace)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.view(n, vocab).cpu().numpy(), logits)
+        assert torch.isnan(buf[:shift]).all() and torch.isnan(buf[shift + n * vocab:]).all()
+
+
 def test_planted_tree(model):
     # Plant the oracle's greedy continuation along the last branch of a 41-node
     # tree; the GPU must accept exactly K nodes and return the next greedy token.
