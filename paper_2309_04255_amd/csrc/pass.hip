@@ -775,27 +775,53 @@ __device__ __forceinline__ bool tile_dispatch_rows(int cw, KParams& p, int step,
 // The B operand of one k-step from its dword of packed codes (see pack.hip):
 // the bf16 values 128 + q_e, formed by placing each code in the low mantissa
 // bits of 128 (exact: 128 + q < 256 has 8 significant bits).
-__device__ __forceinline__ bf16x8 q4_operand(uint32_t w) {
+// mask = 0x000F000F and base = 0x43004300 come in registers: the
+// and-or instruction takes no literals.
+__device__ __forceinline__ bf16x8 q4_operand(uint32_t w, uint32_t mask, uint32_t base) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 v;
 #pragma unroll
-  for (int p2 = 0; p2 < 4; ++p2) v[p2] = ((w >> (4 * p2)) & 0x000F000Fu) | 0x43004300u;
+  for (int p2 = 0; p2 < 4; ++p2) v[p2] = ((w >> (4 * p2)) & mask) | base;
   return __builtin_bit_cast(bf16x8, v);
 }
 
-// 4-bit tile: blocks [nb0, nb0 + C) of a layer step over all its scale
-// groups (128 inputs, four k-steps each), waves taking interleaved groups.
-// Per group the codes enter the matrix cores as 128 + q, and a product with
-// a constant operand of 136 = 128 + 8 gives 136 times the group's sum of
-// activations per row; their difference is sum_k (q_k - 8) a_k exactly as
-// fp32 sums, and the column's scale multiplies it into the accumulator --
-// w = s (q - 8) is never formed.  Structure as tile_compute (weight stages
-// before the barrier, epilogue inputs parked in LDS by the last wave, partial
-// tiles to LDS at the end), with register stages only.
+// Waves of a 4-bit tile: KW of them take interleaved scale groups, 4 / KW
+// split the rows (at 128 rows two halves, so that a wave never keeps more
+// than four row blocks' accumulators; every activation is still read by one
+// wave only, and each code is dequantised 4 / KW times).  The tile leaves KW
+// partial-tile slots.
+__host__ __device__ constexpr int q4_kways(int MB) { return MB >= 8 ? 2 : 4; }
+
+// Widest 4-bit tile: the partial tiles and the epilogue inputs (which the
+// gate/up step does not have) fit the LDS region.
+template <int MB, int EPI>
+constexpr int q4_tile_blocks() {
+  if (MB <= 2) return 8;
+  if (EPI == EPI_SWIGLU) return MB == 4 ? 8 : 7;
+  return MB == 4 ? 6 : 5;
+}
+
+// 4-bit tile: blocks [nb0, nb0 + C) of a layer step over its scale groups
+// [k0, k0 + kn) (128 inputs, four k-steps each).  Per group a product with a
+// constant operand of -136 = -(128 + 8) gives -136 times the group's sum of
+// activations per row, and the codes, entering the matrix cores as 128 + q,
+// accumulate on top of it: sum_k (q_k - 8) a_k in fp32, which the column's
+// scale then multiplies into the accumulator -- w = s (q - 8) is never formed.
+//
+// A layer's codes are a quarter of the bf16 bytes, so most of a tile fits the
+// LDS: before the barrier waves 1-3 copy there the codes and scales of as
+// many groups as the region holds (the partial-tile slots' room too: they are
+// written only after the loop) and load the next D into registers, so that
+// after the barrier little but the activations is waited for.  At the 7B shape
+// QKV / O / gate-up / down loops take 6.8 / 3.3 / 9.5 / 7.8 us at 31 nodes and
+// 20 / 12 / 28 / 30 at 77 (7.5 / 4.7 / 11.4 / 12.6, and, with tiles of one
+// block that read the activations once per block, 56 / 13 / 93 / 35, when all
+// codes came through registers and each wave kept every row block).
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KParams& pin, int step, int layer,
                                                                           int nb0, int wait_phase, char* lds,
-                                                                          GemmLds& gl, int* lds_flag) {
+                                                                          GemmLds& gl, int* lds_flag, int k0, int kn,
+                                                                          int epi_in) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   KParams& p = uniform_params(pin);
@@ -803,31 +829,59 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   layer = wave_uniform(layer);
   nb0 = wave_uniform(nb0);
   wait_phase = wave_uniform(wait_phase);
+  k0 = wave_uniform(k0);
+  kn = wave_uniform(kn);
+  epi_in = wave_uniform(epi_in);
   const TileIn io = tile_in(p, step, layer);
   const int wave = wave_index(), lane = threadIdx.x & 63;
-  const int gs = io.ks;  // scale groups
-  const int ns = wave_uniform(wave < gs ? (gs - wave + kWaves - 1) / kWaves : 0);
+  constexpr int KW = q4_kways(MB), RW = kWaves / KW, RB = MB / RW;
+  const int kw = wave % KW, rw = wave / KW;
+  const int gs = io.ks;  // scale groups of the matrix
+  const int ns = wave_uniform(kw < kn ? (kn - kw + KW - 1) / KW : 0);  // this wave's: k0 + kw + KW i
   constexpr int D = 2;
-  // this wave's groups: wave + 4 i
-  const u32x4* wt = (const u32x4*)io.w + ((size_t)nb0 * gs + wave) * 64 + lane;
+  const u32x4* wt = (const u32x4*)io.w + ((size_t)nb0 * gs + k0 + kw) * 64 + lane;
   const size_t cstride = (size_t)gs * 64;
-  const uint16_t* st = io.sc + ((size_t)nb0 * gs + wave) * kNB + 4 * (lane >> 4);  // (this lane's four columns)
+  const uint16_t* st = io.sc + ((size_t)nb0 * gs + k0 + kw) * kNB + 4 * (lane >> 4);  // (this lane's four columns)
   const size_t sstride = (size_t)gs * kNB;
-  const bf16x8* at = io.a + (size_t)wave * 4 * MB * 64 + lane;
+  const bf16x8* at = io.a + ((size_t)(k0 + kw) * 4 * MB + rw * RB) * 64 + lane;
   const u32x4* zero_w = (const u32x4*)p.zero + lane;
   const uint16_t* zero_s = (const uint16_t*)p.zero;
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
-  const f32x4* zero4 = (const f32x4*)p.zero + lane;
+  // The LDS region: the epilogue inputs, where the step has them, after the
+  // KW partial-tile slots; the scales of the groups kept there at the end;
+  // the codes in the rest (piece 1 before the epilogue inputs, piece 2 after).
+  constexpr int kCap = kGemmLdsBytes / 1024;
+  const bool epi = epi_in && (io.resid || step == STEP_QKV);
+  const int sck = C * (((kn < 160 ? kn : 160) + 31) / 32);  // KiB of scales
+  const int piece1 = epi ? KW * C * MB : kCap - sck;
+  const int base2 = epi ? (KW + 1) * C * MB + C : kCap - sck;
+  const int room2 = kCap - sck - base2 > 0 ? kCap - sck - base2 : 0;
+  const int PA = piece1 / (KW * C);
+  const int wcap = wave_uniform(p.step[step].wl_cap);
+  int pmax = base2 <= kCap - sck ? PA + room2 / (KW * C) : 0;
+  pmax = pmax < wcap ? pmax : wcap;
+  const int nsmin = kn / KW;  // (every wave has at least these)
+  // (for the residual steps; a copy of the QKV or gate/up step's 96 to 130 KiB
+  // per CU delays the barrier's poll, queued behind it, by more than the loop
+  // gains: 2574 and 2564 us per pass without theirs, 2688 with, at the 7B
+  // shape and 31 nodes; without O's 2705, without the down projection's 2770)
+  const int P = wave_uniform(wait_phase >= 0 && io.resid ? (nsmin < pmax ? nsmin : pmax) / D * D : 0);
+  auto code_at = [&](int i, int k, int c) {  // group k0 + k + KW i of block c
+    const int j = i < PA ? (i * KW + k) * C + c : base2 + ((i - PA) * KW + k) * C + c;
+    return lds + (size_t)j * 1024;
+  };
+  char* scl = lds + (size_t)(kCap - sck) * 1024;  // scales [c][sck / C KiB]: group k0 + j at + 32 j
+  const int scb = sck / C * 1024;
   u32x4 bw[D][C];
   u32x2 bs[D][C];
-  bf16x8 ba[D][4][MB];
+  bf16x8 ba[D][4][RB];
   auto load_w = [&](int slot, int i) {  // group i of this wave, or the zero line past the last
     const bool live = i < ns;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
       bw[slot][c] = __builtin_nontemporal_load(
-          (const LLMCAD_GLOBAL u32x4*)opaque(live ? wt + c * cstride + (size_t)(kWaves * i) * 64 : zero_w));
-      bs[slot][c] = ldg((const u32x2*)opaque(live ? st + c * sstride + (size_t)(kWaves * i) * kNB : zero_s));
+          (const LLMCAD_GLOBAL u32x4*)opaque(live ? wt + c * cstride + (size_t)(KW * i) * 64 : zero_w));
+      bs[slot][c] = ldg((const u32x2*)opaque(live ? st + c * sstride + (size_t)(KW * i) * kNB : zero_s));
     }
   };
   auto load_a = [&](int slot, int i) {
@@ -835,39 +889,46 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int rb = 0; rb < MB; ++rb)
-        ba[slot][t][rb] = ldg(opaque(live ? at + ((size_t)kWaves * 4 * i * MB + t * MB + rb) * 64 : zero));
+      for (int rb = 0; rb < RB; ++rb)
+        ba[slot][t][rb] = ldg(opaque(live ? at + ((size_t)KW * 4 * i * MB + t * MB + rb) * 64 : zero));
   };
-  // Epilogue inputs, by the last wave before the barrier (as tile_compute).
-  constexpr int KU = C * MB;
-  constexpr int kEpiWave = kWaves - 1;
-  if (wave == kEpiWave) {
-    f32x4 sx[KU], sg[C];
-    const bool resid = io.resid;
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int c = u / MB, rb = u % MB;
-      const int col0 = kNB * (nb0 + c);
-      const f32x4* src = zero4;
-      if (resid) {
-        src = (const f32x4*)(io.x_in + (size_t)(16 * rb + (lane >> 2)) * p.d + col0 + 4 * (lane & 3));
-      } else if (step == STEP_QKV && col0 < 2 * p.d) {
-        const int t = (col0 % p.d % p.Dh) / kNB;
-        src = (const f32x4*)(p.rope + ((size_t)(16 * rb + (lane >> 2)) * (p.Dh / 2) + 8 * t + 2 * (lane & 3)) * 2);
+  // Before the barrier, by waves 1-3 (wave 0 polls it with no load in flight):
+  // the epilogue inputs (residual rows or rotary table, and the next norm's
+  // gains; written two or more phases ago), the scales, and the codes of the
+  // first P groups of every wave, straight to LDS; then this wave's next D
+  // groups into registers.
+  if (wave != 0) {
+    if (epi) {
+      char* eb = lds + epi_off(C, MB, KW);
+      for (int u = wave - 1; u < C * MB; u += kWaves - 1) {
+        const int c = u / MB, rb = u % MB;
+        const int col0 = kNB * (nb0 + c);
+        const char* src = p.zero + lane * 16;
+        if (io.resid) {  // residual rows 16 rb + l / 4, columns col0 + 4 (l % 4) .. + 3
+          src = (const char*)(io.x_in + (size_t)(16 * rb + (lane >> 2)) * p.d + col0 + 4 * (lane & 3));
+        } else if (col0 < 2 * p.d) {  // (cos, sin) of pairs 8 t + 2 (l % 4), + 1
+          const int t = (col0 % p.d % p.Dh) / kNB;
+          src = (const char*)(p.rope + ((size_t)(16 * rb + (lane >> 2)) * (p.Dh / 2) + 8 * t + 2 * (lane & 3)) * 2);
+        }
+        dma16(src, eb + (size_t)u * 1024);
       }
-      sx[u] = ldg(opaque(src));
+      if (io.resid)
+        for (int c = wave - 1; c < C; c += kWaves - 1)
+          dma16(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1), eb + (size_t)(C * MB + c) * 1024);
+    }
+    const int sbytes = P * KW * 32;  // of one block's scales
+    for (int u = wave - 1; u < sck; u += kWaves - 1) {
+      const int c = u / (sck / C), o = (u % (sck / C)) * 1024 + lane * 16;
+      if (u % (sck / C) * 1024 < sbytes)
+        dma16(o < sbytes ? (const char*)(io.sc + ((size_t)(nb0 + c) * gs + k0) * kNB) + o : p.zero + lane * 16,
+              scl + (size_t)u * 1024);
+    }
+    for (int u = wave - 1; u < P * KW * C; u += kWaves - 1) {
+      const int c = u % C, k = (u / C) % KW, i = u / (C * KW);
+      dma16((const u32x4*)io.w + ((size_t)(nb0 + c) * gs + k0 + k + KW * i) * 64 + lane, code_at(i, k, c));
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c)
-      sg[c] = ldg(opaque(resid ? (const f32x4*)(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1)) : zero4));
-#pragma unroll
-    for (int u = 0; u < KU; ++u) lds_st<f32x4>(lds + epi_off(C, MB, 4) + (size_t)u * 1024 + lane * 16, sx[u]);
-#pragma unroll
-    for (int c = 0; c < C; ++c) lds_st<f32x4>(lds + epi_off(C, MB, 4) + (size_t)(C * MB + c) * 1024 + lane * 16, sg[c]);
-  }
-  if (wave != 0) {
-#pragma unroll
-    for (int u = 0; u < D; ++u) load_w(u, u);
+    for (int u = 0; u < D; ++u) load_w(u, P + u);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0) {
@@ -880,6 +941,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   constexpr int SSQN = SSQR ? 8 : 1;
   f32x4 sr[SSQN];
   if constexpr (SSQR) {
+    const f32x4* zero4 = (const f32x4*)p.zero + lane;
     constexpr int QUADS = 4 * MB, CH = 256 / QUADS;
     const int q = threadIdx.x % QUADS, ch = threadIdx.x / QUADS;
     const int t0 = ch * p.d_nb / CH, t1 = (ch + 1) * p.d_nb / CH;
@@ -894,55 +956,79 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   lds_barrier();
   if (wave == 0) {
 #pragma unroll
-    for (int u = 0; u < D; ++u) load_w(u, u);
+    for (int u = 0; u < D; ++u) load_w(u, P + u);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0 && p.trace != nullptr && threadIdx.x == 0)
     stg(p.trace + (size_t)blockIdx.x * pass_phases(p.L) * 8 + wait_phase * 8 + 3, (long long)wall_clock64());
 
-  f32x4 acc[MB][C];
+  f32x4 acc[RB][C];
 #pragma unroll
-  for (int rb = 0; rb < MB; ++rb)
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[rb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 c136;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) c136[e] = (bf16)136.0f;
-  auto group = [&](int u) {  // the group in stage u, into acc
-    f32x4 tmp[MB][C], corr[MB];
+  for (int e = 0; e < 8; ++e) c136[e] = (bf16)-136.0f;
+  uint32_t qmask = 0x000F000Fu, qbase = 0x43004300u;
+  asm volatile("" : "+s"(qmask), "+v"(qbase));  // (kept in registers: see q4_operand)
+  // one group's products from activation stage u, codes w and scales s, into acc
+  auto group = [&](int u, const u32x4 (&w)[C], const u32x2 (&sv)[C]) {
+    f32x4 corr[RB];
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) {
-      corr[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RB; ++rb) corr[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < C; ++c) tmp[rb][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      bf16x8 b[C];
+      for (int rb = 0; rb < RB; ++rb) corr[rb] = mfma16x16x32(c136, ba[u][t][rb], corr[rb]);
+    // (blocks in pairs: enough independent products in flight, few registers)
 #pragma unroll
-      for (int c = 0; c < C; ++c) b[c] = q4_operand(bw[u][c][t]);
+    for (int c0 = 0; c0 < C; c0 += 2) {
+      constexpr int PC = 2;
+      f32x4 tmp[RB][PC];
 #pragma unroll
-      for (int rb = 0; rb < MB; ++rb) {
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int c = 0; c < C; ++c) tmp[rb][c] = mfma16x16x32(b[c], ba[u][t][rb], tmp[rb][c]);
-        corr[rb] = mfma16x16x32(c136, ba[u][t][rb], corr[rb]);
-      }
-    }
+        for (int j = 0; j < PC; ++j)
+          if (c0 + j < C) {
+            const bf16x8 b = q4_operand(w[c0 + j][t], qmask, qbase);
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      // the four columns' bf16 scales
-      const f32x4 sc = {__uint_as_float(bs[u][c][0] << 16), __uint_as_float(bs[u][c][0] & 0xFFFF0000u),
-                        __uint_as_float(bs[u][c][1] << 16), __uint_as_float(bs[u][c][1] & 0xFFFF0000u)};
+            for (int rb = 0; rb < RB; ++rb) tmp[rb][j] = mfma16x16x32(b, ba[u][t][rb], t == 0 ? corr[rb] : tmp[rb][j]);
+          }
 #pragma unroll
-      for (int rb = 0; rb < MB; ++rb) acc[rb][c] += sc * (tmp[rb][c] - corr[rb]);
+      for (int j = 0; j < PC; ++j)
+        if (c0 + j < C) {
+          // the four columns' bf16 scales
+          const u32x2 s2 = sv[c0 + j];
+          const f32x4 sc = {__uint_as_float(s2[0] << 16), __uint_as_float(s2[0] & 0xFFFF0000u),
+                            __uint_as_float(s2[1] << 16), __uint_as_float(s2[1] & 0xFFFF0000u)};
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) acc[rb][c0 + j] += sc * tmp[rb][j];
+        }
     }
   };
   int i = 0;
+  for (; i < P; i += D) {  // codes in LDS: only activations in flight
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      __builtin_amdgcn_sched_barrier(0);
+      u32x4 w[C];
+      u32x2 sv[C];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        w[c] = lds_ld<u32x4>(code_at(i + u, kw, c) + lane * 16);
+        sv[c] = lds_ld<u32x2>(scl + (size_t)c * scb + (size_t)(kw + KW * (i + u)) * 32 + 8 * (lane >> 4));
+      }
+      group(u, w, sv);
+      __builtin_amdgcn_sched_barrier(0);
+      load_a(u, i + u + D);
+    }
+  }
   for (; i + D < ns; i += D) {
 #pragma unroll
     for (int u = 0; u < D; ++u) {
       __builtin_amdgcn_sched_barrier(0);
-      group(u);
+      group(u, bw[u], bs[u]);
       __builtin_amdgcn_sched_barrier(0);
       load_w(u, i + u + D);
       load_a(u, i + u + D);
@@ -952,7 +1038,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 #pragma unroll
     for (int u = 0; u < D; ++u) {
       __builtin_amdgcn_sched_barrier(0);
-      group(u);
+      group(u, bw[u], bs[u]);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -966,21 +1052,22 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
       *(f32x4*)&gl.part_ss[ch * 16 * MB + 4 * q] = t;
     }
   }
+  lds_barrier();  // (the slots' room may hold codes another wave still reads)
 #pragma unroll
   for (int c = 0; c < C; ++c)
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb)
-      lds_st<f32x4>(lds + tw_off() + ((size_t)((wave * C + c) * MB + rb) * 64 + lane) * 16, acc[rb][c]);
+    for (int rb = 0; rb < RB; ++rb)
+      lds_st<f32x4>(lds + tw_off() + ((size_t)((kw * C + c) * MB + rw * RB + rb) * 64 + lane) * 16, acc[rb][c]);
   __syncthreads();
   return true;
 }
 
 template <int MB, int C>
 __device__ __forceinline__ bool tile_dispatch_q4(int cw, KParams& p, int step, int layer, int nb0, int wait_phase,
-                                                 char* lds, GemmLds& gl, int* flag) {
+                                                 char* lds, GemmLds& gl, int* flag, int k0, int kn, int epi_in) {
   if constexpr (C >= 1) {
-    if (cw == C) return tile_compute_q4<MB, C>(p, step, layer, nb0, wait_phase, lds, gl, flag);
-    return tile_dispatch_q4<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, gl, flag);
+    if (cw == C) return tile_compute_q4<MB, C>(p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
+    return tile_dispatch_q4<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
   } else {
     return false;
   }
@@ -1588,7 +1675,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
 // One GEMM phase: this workgroup's run of blocks, in tiles over the full K
 // (K-split tiles of up to 8, 6 or 4 blocks at 32, 64 or 128 rows; row-split
 // tiles of up to 8 where a run exceeds one K-split tile at 64+ rows; 4-bit
-// tiles of up to 6, 2 or 1), each followed by its epilogue.  The LM head then
+// tiles of up to 8, 6 or 5, gate/up's up to 8 or 7), each followed by its epilogue.  The LM head then
 // publishes the workgroup's argmax per row, and the last workgroup to do so
 // runs the accept walk.
 template <int MB, int EPI, int CM2 = 8>
@@ -1607,8 +1694,9 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
   static_assert(wl_off(CM, MB, tile_slots(CM, MB)) <= kGemmLdsBytes,
                 "a tile's partial sums and epilogue inputs fit the LDS");
   static_assert(EPI != EPI_LOGITS || CM2 <= 8, "the LM head's per-block argmax slots");
-  // 4-bit tiles hold a second set of accumulators (each group's partial sums)
-  constexpr int CMQ = MB <= 2 ? 6 : MB == 4 ? 2 : 1;
+  constexpr int CMQ = q4_tile_blocks<MB, EPI>();
+  static_assert((EPI == EPI_SWIGLU ? epi_off(CMQ, MB, q4_kways(MB)) : wl_off(CMQ, MB, q4_kways(MB))) <= kGemmLdsBytes,
+                "a 4-bit tile's partial sums and epilogue inputs fit the LDS");
   // Row-split tiles (up to 8 blocks) for a workgroup of a pass of 64+ rows
   // whose blocks do not fit one K-split tile: it then reads the activations
   // once instead of once per tile (where one K-split tile holds them all,
@@ -1641,18 +1729,20 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
     const bool first = b0 == lo;
     bool ok;
     if constexpr (MB >= 4) {
-      ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag)
+      ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
+                                              sp.ksteps, 1)
            : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, lds, lds_flag)
                   : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
                                           sp.ksteps, 1);
     } else {
-      ok = q4 ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag)
+      ok = q4 ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
+                                          sp.ksteps, 1)
               : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
                                       sp.ksteps, 1);
     }
     if (!ok) return false;
     if (first) trace_mark(sy, phase, 4);
-    finish_tile<MB, EPI>(p, step, layer, b0, cw, lds, gl, q4 ? 4 : rows ? 1 : tile_slots(cw, MB));
+    finish_tile<MB, EPI>(p, step, layer, b0, cw, lds, gl, q4 ? q4_kways(MB) : rows ? 1 : tile_slots(cw, MB));
   }
   trace_mark(sy, phase, 5);
   if constexpr (EPI == EPI_LOGITS) {

@@ -323,6 +323,29 @@ def test_prefill_last_logits(model):
     parity.check_logits(out.cpu().numpy()[None], ref[-1:], "prefill")
 
 
+@pytest.mark.parametrize("d_ffn", [5120, 5248])
+def test_q4_long_rows(monkeypatch, d_ffn):
+    # 4-bit tiles with many scale groups per row (40, and 41: one more than the
+    # waves divide evenly): a workgroup's first groups come from the LDS, in
+    # both pieces of its region, the rest through registers.  Small grids give
+    # tiles of several blocks, whose codes exceed the region; 1 to 8 row blocks.
+    binding = _gpu()
+    shape = workloads.ModelShape("q4long", 2, 512, 4, 128, d_ffn, 1000, seed=0x5EED0140, weight_bits=4)
+    gen = workloads.make_weights(shape, "cuda", gain_jitter=0.1)
+    sess = binding.Session(shape, capacity=256)
+    sess.load_weights(gen)
+    m = types.SimpleNamespace(shape=shape, sess=sess, ow=oracle_weights(shape, gain_jitter=0.1), binding=binding)
+    prefix = workloads.draw_tokens(P, shape.vocab, seed=3)
+    m.ok, m.ov = oracle.prefill_kv(m.ow, prefix, rounding=True)
+    sess.prefill(prefix, 0)
+    for tree in ("chain_n9", "binary_d4_n31", "b432_n41", "random_n128"):
+        tok = workloads.draw_tokens(len(TREES[tree]), shape.vocab, seed=31)
+        for grid in ("256", "32", "8"):
+            monkeypatch.setenv("LLMCAD_PASS_GRID", grid)
+            logits = _check_all(m, TREES[tree], tok, f"F={d_ffn} {tree} grid {grid}")
+            np.testing.assert_array_equal(logits, _run(m, TREES[tree], tok)[0])
+
+
 @pytest.mark.parametrize("vocab", [1003, 1006, 1020, 1024])
 def test_logit_columns(vocab):
     # The LM head's epilogue stores four columns of a row in one piece where
