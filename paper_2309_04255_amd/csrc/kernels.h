@@ -109,6 +109,7 @@ struct PassParams {
   int* accept_len;
   int* next_token;
   // control
+  int kv_only;       // 1: nothing reads the pass's outputs but its keys and values: it ends with the last layer's
   int spin_limit;    // bound of every wait loop (polls)
   int attn_prefetch; // 1: the attention fetches its prefix steps before its barrier (0: all after)
   int row_tiles;     // 1: GEMM phases of passes of 64+ rows take row-split tiles (waves split rows)

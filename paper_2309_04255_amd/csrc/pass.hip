@@ -227,7 +227,10 @@ struct GemmLds {
     float red_s[kMaxNodes][8];  // LM head: sum of exp(logit - red_v) per (row, block of the tile)
   };
   float red_v[kMaxNodes][8];    // LM head: argmax per (row, block of the tile)
-  int red_i[kMaxNodes][8];
+  union {
+    float part_ss2[512];        // the partial sums' sums by part
+    int red_i[kMaxNodes][8];
+  };
   float best_v[kMaxNodes];      // LM head: argmax per row over this workgroup's blocks
   int best_i[kMaxNodes];
   int reach[kMaxNodes];         // accept walk: reachability of each node,
@@ -1089,12 +1092,37 @@ __device__ __forceinline__ float rope_inv_freq(int j, int Dh, float log2_theta) 
   return exp2f(-(2.0f * (float)j / (float)Dh) * log2_theta);
 }
 
-// RMSNorm scales of rows [0, Mp): 1 / sqrt(mean of squares + eps) from the
-// per-16-column sums of squares the producing phase wrote, added in a fixed
-// order; 0 for rows >= n.  When the tile held them in registers its chunk
-// sums are in part_ss already.
-// RMSNorm scales of rows [0, Mp) into gl.rstd from a version's sums of
-// squares ssq [d/16][Mp] (added in a fixed order); 0 for rows >= n.
+// RMSNorm scales of rows [0, Mp) into gl.rstd, 1 / sqrt(mean of squares +
+// eps), 0 for rows >= n, from the chunk sums in gl.part_ss ([64 / MB][16 MB]):
+// thread t adds the four of row t % (16 MB), part t / (16 MB); the parts meet
+// across the wave, then (gl.part_ss2) across the waves, in a fixed order.  (One
+// thread per row adding up to 64 chunks in turn: +0.2 us per epilogue.)
+template <int MB>
+__device__ __forceinline__ void chunk_scales(KParams& p, GemmLds& gl) {
+  constexpr int ROWS = 16 * MB, NP = ROWS < 64 ? kWaves : kThreads / ROWS;
+  const int row = threadIdx.x % ROWS, part = threadIdx.x / ROWS;
+  float t = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) t += gl.part_ss[(4 * part + e) * ROWS + row];
+  if constexpr (MB == 1) {
+    t = col4_sum(t);
+  } else if constexpr (MB == 2) {
+    float a, b;
+    pair_xor32(t, a, b);
+    t = a + b;
+  }
+  if (ROWS >= 64 || (threadIdx.x & 63) < ROWS) gl.part_ss2[(ROWS < 64 ? wave_index() : part) * ROWS + row] = t;
+  __syncthreads();
+  if (threadIdx.x < ROWS) {
+    float u = 0.0f;
+#pragma unroll
+    for (int k = 0; k < NP; ++k) u += gl.part_ss2[k * ROWS + threadIdx.x];
+    gl.rstd[threadIdx.x] = threadIdx.x < p.n ? 1.0f / sqrtf(u * p.inv_d + p.eps) : 0.0f;
+  }
+  __syncthreads();
+}
+
+// The same from a version's sums of squares ssq [d/16][Mp].
 template <int MB>
 __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq, GemmLds& gl) {
   // thread t: rows 4 q .. 4 q + 3 (q = t % (ROWS / 4)) of the 16-column blocks
@@ -1115,28 +1143,17 @@ __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq, GemmLds& 
   }
   *(f32x4*)&gl.part_ss[ch * ROWS + 4 * q] = ss;
   __syncthreads();
-  if (threadIdx.x < ROWS) {
-    float t = 0.0f;
-    for (int c = 0; c < CHK; ++c) t += gl.part_ss[c * ROWS + threadIdx.x];
-    gl.rstd[threadIdx.x] = threadIdx.x < p.n ? 1.0f / sqrtf(t * p.inv_d + p.eps) : 0.0f;
-  }
-  __syncthreads();
+  chunk_scales<MB>(p, gl);
 }
 
+// A norm step's row scales; when its tile held the sums of squares in
+// registers the chunk sums are in part_ss already.
 template <int MB>
 __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io, GemmLds& gl) {
-  constexpr int ROWS = 16 * MB;
-  if (MB <= 2 && p.ssq_regs) {
-    constexpr int CH = 256 / (4 * MB);
-    if (threadIdx.x < ROWS) {
-      float t = 0.0f;
-      for (int c = 0; c < CH; ++c) t += gl.part_ss[c * ROWS + threadIdx.x];
-      gl.rstd[threadIdx.x] = threadIdx.x < p.n ? 1.0f / sqrtf(t * p.inv_d + p.eps) : 0.0f;
-    }
-    __syncthreads();
-    return;
-  }
-  row_rstd<MB>(p, io.ssq, gl);
+  if (MB <= 2 && p.ssq_regs)
+    chunk_scales<MB>(p, gl);
+  else
+    row_rstd<MB>(p, io.ssq, gl);
 }
 
 // Epilogue of one accumulator tile ("unit": block c of the tile x row block
@@ -1431,9 +1448,22 @@ __device__ __attribute__((noinline, not_tail_called)) void finish_candidates(KPa
     if (wave == 0) {
       float m = -INFINITY, s = 0.0f;
       int ix = 0x7fffffff;
-      for (int t = lane; t < entries; t += 64)
-        softmax_merge(m, s, ix, ld_coherent(&p.lm_val[(size_t)r * G + t]), ld_coherent(&p.lm_sum[(size_t)r * G + t]),
-                      ld_coherent(&p.lm_idx[(size_t)r * G + t]));
+      constexpr int PB = 4;  // partials per lane loaded in one round trip
+      for (int t0 = lane; t0 < entries; t0 += 64 * PB) {
+        float pm[PB], ps[PB];
+        int pi[PB];
+#pragma unroll
+        for (int k = 0; k < PB; ++k) {
+          const int t = t0 + 64 * k;
+          const size_t at = (size_t)r * G + (t < entries ? t : t0);
+          pm[k] = ld_coherent(&p.lm_val[at]);
+          ps[k] = ld_coherent(&p.lm_sum[at]);
+          pi[k] = ld_coherent(&p.lm_idx[at]);
+        }
+#pragma unroll
+        for (int k = 0; k < PB; ++k)
+          if (t0 + 64 * k < entries) softmax_merge(m, s, ix, pm[k], ps[k], pi[k]);
+      }
 #pragma unroll
       for (int off = 32; off >= 1; off >>= 1) {
         const float om = __shfl_xor(m, off, kWave), os = __shfl_xor(s, off, kWave);
@@ -1451,13 +1481,27 @@ __device__ __attribute__((noinline, not_tail_called)) void finish_candidates(KPa
     const float M = sm[0], S = sm[1], thr = p.cand_thr;
     const int amax = si[0];
     const float* row = p.logits + (size_t)(r - p.row_lo) * V;
-    for (int v = threadIdx.x; v < V; v += kThreads) {
-      const float pr = expf(ld_coherent(row + v) - M) / S;
-      if (pr > thr || v == amax) {
-        const int k = atomicAdd(&si[1], 1);
-        if (k < LLMCAD_CAND_MAX) {
-          ctok[k] = v;
-          cprob[k] = pr;
+    // The scan is one workgroup's, at the end of the pass: a batch of loads in
+    // flight per thread (one at a time, a row of 32000 logits took ~50 us of a
+    // draft step, 4%), and a bound on the logit, below the threshold by more
+    // than any rounding, spares the exponential of the others.
+    const float cut = M + logf(thr * S) - (0.01f + 1e-6f * fabsf(M));
+    constexpr int VB = 32;
+    for (int v0 = threadIdx.x; v0 < V; v0 += kThreads * VB) {
+      float x[VB];
+#pragma unroll
+      for (int k = 0; k < VB; ++k) x[k] = ld_coherent(row + (v0 + kThreads * k < V ? v0 + kThreads * k : v0));
+#pragma unroll
+      for (int k = 0; k < VB; ++k) {
+        const int v = v0 + kThreads * k;
+        if (v >= V || (x[k] < cut && v != amax)) continue;
+        const float pr = expf(x[k] - M) / S;
+        if (pr > thr || v == amax) {
+          const int e = atomicAdd(&si[1], 1);
+          if (e < LLMCAD_CAND_MAX) {
+            ctok[e] = v;
+            cprob[e] = pr;
+          }
         }
       }
     }
@@ -2355,7 +2399,8 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
 
   for (int l = 0; l < p.L && ok; ++l) {
     ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
-    if (!ok) break;
+    // (a pass that only fills the cache ends with the last layer's keys and values)
+    if (!ok || (p.kv_only && l == p.L - 1)) break;
     grid_arrive(sy, phase++);
     ok = attn_phase<MB, DH>(p, l, phase, lds_raw, &flag);
     if (!ok) break;
@@ -2373,8 +2418,8 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
     if (!ok) break;
     grid_arrive(sy, phase++);
   }
-  if (ok) ok = final_norm_phase<MB>(p, phase, gl, &flag);
-  if (ok) {  // LM head + argmax + accept walk
+  if (ok && !p.kv_only) ok = final_norm_phase<MB>(p, phase, gl, &flag);
+  if (ok && !p.kv_only) {  // LM head + argmax + accept walk
     grid_arrive(sy, phase++);
     if (gemm_phase<MB, EPI_LOGITS>(p, STEP_LM, 0, phase, lds_raw, gl, &flag)) trace_mark(sy, phase, 2);
   }

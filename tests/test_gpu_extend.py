@@ -149,3 +149,26 @@ def test_candidate_records_overflow(model):
         assert rec["count"] == -1 and rec["tok"] == [] and rec["prob"] == []
         assert rec["argmax"] == int(np.argmax(rows[r]))
         assert rec["max_logit"] == float(rows[r].max())
+
+
+@pytest.mark.parametrize("n", [9, 40, 150])
+def test_cache_only_passes(model, n):
+    # A tree-decoder step or a prefill whose logits nobody asked for ends with
+    # the last layer's keys and values: the cache holds the same bits as after
+    # the call that returns them (one chunk, and two for 150 tokens), and
+    # nothing else of the cache is touched.
+    from paper_2309_04255_amd import binding
+
+    s = model.sess
+    tok = workloads.draw_tokens(n, model.shape.vocab, seed=91, stream=n)
+    runs = []
+    for want in (True, False):
+        k, v = torch.full_like(s.k_cache, 7.0), torch.full_like(s.v_cache, 7.0)
+        binding.prefill(s.cfg, s.packed, k, v, tok, 0, s.last_logits if want else None, s.workspace)
+        if n <= 40:
+            parent = workloads.random_tree(n, 7, n)
+            binding.extend_tree(s.cfg, s.packed, k, v, n, tok, parent, n // 2, s.logits if want else None, s.workspace)
+        s.check()
+        runs.append((k, v))
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
+    assert not torch.any(runs[1][0][:, :, :n] == 7.0) and torch.all(runs[1][0][:, :, 2 * n:] == 7.0)
