@@ -175,6 +175,9 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   p.prefix_len = a.prefix_len;
   p.cap = a.cap;
   p.G = G;
+  p.gshift = -1;
+  for (int k = 0; k < 11; ++k)
+    if (G == 1 << k) p.gshift = k;
   p.packed = a.packed;
   p.o_embed = (long long)P.embed;
   p.o_final_norm = (long long)P.final_norm;
@@ -197,24 +200,43 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
     sp.split = 1;
     sp.wide = i == STEP_GATE_UP && wide ? 1 : 0;
   }
-  // Split-K for the projections with one column block per workgroup (O and
-  // down: d/16 blocks): groups of S workgroups share a group's blocks, each
-  // over 1/S of the k-steps, so each reads 1/S of the activations per block
-  // of weights; the partial tiles meet in memory and each workgroup finishes
-  // 1/S of the group's blocks.  It pays where the activations outweigh the
-  // weights by far: the down projection (K = F) of passes of 64 or more rows,
-  // in pairs (measured at the LLaMA-7B shape: -3.5% per pass at 41 and 128
-  // rows; at 32 rows, and for O, the hand-off costs more than it saves).
-  // (LLMCAD_SPLIT_O / LLMCAD_SPLIT_DOWN, diagnostics, ask for 1, 2 or 4.)
+  // Split-K: groups of S workgroups share a group of column blocks, each over
+  // 1/S of the k-steps, so each reads 1/S of the activations per block of
+  // weights; the partial tiles meet in memory and each workgroup finishes 1/S
+  // of the group's blocks.  The region for the partial tiles runs from the
+  // attention's to the end of split-K's own.
+  p.row_tiles = env_int("LLMCAD_ROW_TILES", 1) == 2 ? 0 : 1;  // (diagnostics: 2 turns the row-split tiles off)
+  const size_t part_room = (W.part - W.attn_o) / ((size_t)W.Mp / 16 * 1024) + W.part_slots;
   {
-    const int want[2] = {env_int("LLMCAD_SPLIT_O", 1), env_int("LLMCAD_SPLIT_DOWN", W.Mp >= 64 ? 2 : 1)};
-    const int steps[2] = {STEP_O, STEP_DOWN};
-    for (int j = 0; j < 2; ++j) {
-      StepPlan& sp = p.step[steps[j]];
-      const int S = want[j];
-      if ((S == 2 || S == 4) && !sp.q4 && G % S == 0 && sp.nblocks >= G / S &&
-          (size_t)G * cdiv(sp.nblocks, G / S) <= W.part_slots)
-        sp.split = S;
+    // At 128 rows a CU's loads bound every step (see split_rows_phase): QKV in
+    // pairs, O and the down projection in fours (7B: 5383 us per pass without
+    // QKV's, 5308 without O's, 5264 with all; the down projection in pairs
+    // 5605, in eights 5422 against 5318 in fours).  Not gate/up, whose groups'
+    // partial tiles are the largest and whose weights alone take two thirds of
+    // the time.
+    // At 64 rows: the down projection in pairs (-3.5% per pass at 41 rows; at
+    // 32 rows, and for O, the hand-off costs more than it saves).
+    // (LLMCAD_SPLIT_QKV / _O / _GU / _DOWN, diagnostics, ask for 1, 2, 4 or 8.)
+    const char* names[4] = {"LLMCAD_SPLIT_QKV", "LLMCAD_SPLIT_O", "LLMCAD_SPLIT_GU", "LLMCAD_SPLIT_DOWN"};
+    const int rows_s[4] = {2, 4, 1, 4};                  // with row-split tiles
+    const int k_s[4] = {1, 1, 1, W.Mp >= 64 ? 2 : 1};  // with K-split tiles
+    for (int j = 0; j < 4; ++j) {
+      StepPlan& sp = p.step[j];
+      if (sp.q4) continue;
+      // groups of S workgroups with at least a block each, whose partial tiles fit the region
+      auto groups = [&](int S) {
+        return (S == 2 || S == 4 || S == 8) && G % S == 0 && G / S <= kSplitGroups && sp.nblocks >= G / S &&
+               (size_t)G * cdiv(sp.nblocks, G / S) <= part_room;
+      };
+      const int want = env_int(names[j], 0);
+      const int R = want > 0 ? want : rows_s[j], K = want > 0 ? want : k_s[j];
+      if (W.Mp == 128 && p.row_tiles && groups(R) &&
+          split_rows_fits(cdiv(sp.nblocks, G / R), cdiv(cdiv(sp.nblocks, G / R), R), j != STEP_GATE_UP)) {
+        sp.split = R;
+        sp.split_rows = 1;
+      } else if ((j == STEP_O || j == STEP_DOWN) && K <= kMaxSplitK && groups(K)) {
+        sp.split = K;
+      }
     }
   }
   p.k_cache = (bf16*)a.k_cache;
@@ -250,7 +272,7 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   p.attn_o = (float*)(ws + W.attn_o);
   p.attn_ml = (float*)(ws + W.attn_ml);
   p.head_cnt = (int*)(ws + W.head_counters());
-  p.part = (float*)(ws + W.part);
+  p.part = (float*)(ws + W.attn_o);
   p.grp_cnt = (int*)(ws + W.group_counters());
   p.lm_cnt = (int*)(ws + W.lm_cnt());
   p.exit_cnt = (int*)(ws + W.exit_cnt());
@@ -282,8 +304,6 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   }
   // (diagnostics: LLMCAD_ATTN_PREFETCH=2 fetches every attention step after the barrier)
   p.attn_prefetch = env_int("LLMCAD_ATTN_PREFETCH", 1) == 2 ? 0 : 1;
-  // (diagnostics: LLMCAD_ROW_TILES=2 turns the row-split tiles off)
-  p.row_tiles = env_int("LLMCAD_ROW_TILES", 1) == 2 ? 0 : 1;
   p.trace = env_int("LLMCAD_TRACE", 0) ? (long long*)(ws + W.trace) : nullptr;
   TimedLaunch tl(LLMCAD_KERNEL_PASS, a.st);
   HIP_TRY(launch_pass(MB, p, tree, a.st));

@@ -45,7 +45,8 @@ struct StepPlan {
   long long s_off;      // 4-bit: the packed scales, offset as w_off
   int layer_rel;        // 1 if w_off is relative to the layer's start
   int q4;               // 1: 4-bit codes with group scales
-  int split;            // split-K: workgroups sharing each group of column blocks (1: none; 2 or 4)
+  int split;            // split-K: workgroups sharing each group of column blocks (1: none; 2, 4 or 8)
+  int split_rows;       // 1: its split-K runs row-split tiles (128-row passes)
   int wl_cap;           // weight stages per wave copied to LDS before the step's barrier, at most
   int wide;             // 16- and 32-row passes: tiles of up to 9 blocks instead of 8
 };
@@ -60,6 +61,7 @@ struct PassParams {
   // nodes [0, m0) were computed by earlier passes, their K/V are in slots
   // prefix_len + i
   int n, Mp, prefix_len, cap, G;
+  int gshift;  // log2 G, or -1 when G is not a power of two
   int m0, nt;
   // packed weights
   const char* packed;
@@ -92,8 +94,9 @@ struct PassParams {
   int attn_splits;  // KS, key splits per (head, row block): 1 to 4 (the split's 32-key steps contiguous)
   int* head_cnt;    // [H][MB] arrivals of the key splits
   float* part;      // split-K partial tiles: per workgroup w, [cdiv(blocks, G/S)][MB] x 1 KiB
-                    // (fp32 [64 lanes][4]) from slot w cdiv(blocks, G/S)
-  int* grp_cnt;     // [O, down][kPassMaxGrid / 2] arrivals of the workgroups of each split-K group
+                    // (fp32 [64 lanes][4]) from slot w cdiv(blocks, G/S); the attention's partials
+                    // share the region (each is written and read within its phase)
+  int* grp_cnt;     // [QKV, O, gate/up, down][kSplitGroups] arrivals of the workgroups of each split-K group
   float* lm_val;    // [Mp][G] LM-head argmax per row and workgroup
   int* lm_idx;
   float* lm_sum;    // [Mp][G] sum of exp(logit - the workgroup's max) over its columns (with cand)
@@ -118,6 +121,9 @@ struct PassParams {
 
 // mb16: 16-row blocks of the pass (Mp / 16: 1, 2, 4 or 8).
 hipError_t launch_pass(int mb16, const PassParams& p, const TreeArgs& tree, hipStream_t st);
+// Whether a group of cw blocks, of which a workgroup finishes up to oc, fits one
+// row-split tile of a 128-row pass (epi: the step has epilogue inputs).
+bool split_rows_fits(int cw, int oc, bool epi);
 int pass_occupancy(int mb16, int dh, bool wide);  // resident workgroups per CU (0 if unavailable)
 size_t pass_lds_bytes(int mb16, int dh);
 

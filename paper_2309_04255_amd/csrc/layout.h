@@ -24,7 +24,9 @@ constexpr int kQ4ScaleBytes = kNB * 2;
 constexpr int kMaxNodes = LLMCAD_MAX_NODES;
 constexpr int kAttnMaxSplits = 4;   // key splits per (head, 16-row block)
 constexpr int kMaxSplitK = 4;       // workgroups sharing the k-steps of a group of column blocks
+constexpr int kMaxRowSplit = 8;     // the same at 128 rows with row-split tiles
 constexpr int kPassMaxGrid = 1024;  // workgroups of the pass
+constexpr int kSplitGroups = 256;   // groups of one split-K step, at most
 constexpr int kBarSlots = 16;       // grid-barrier counters
 constexpr int kBarStride = 32;      // ints between barrier counters (128 bytes)
 constexpr int kZeroBytes = 4096;    // zeros (padding reads)
@@ -189,7 +191,7 @@ struct WorkspaceLayout {
     // that their offsets do not depend on the pass's node count or grid:
     // llmcad_workspace_init clears them once for every later pass.
     n_head_counters = s.H * (kMaxNodes / 16);
-    n_group_counters = kPassMaxGrid;  // [O, down][up to G / 2 groups]
+    n_group_counters = 4 * kSplitGroups;  // [QKV, O, gate/up, down][groups]
     counters_bytes = (size_t)(n_head_counters + 4 + n_group_counters) * 4;
     counters = take(counters_bytes);
     bar = take((size_t)kBarSlots * kBarStride * 4);

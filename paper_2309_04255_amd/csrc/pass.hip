@@ -71,6 +71,9 @@ constexpr int kThreads = 64 * kWaves;
 #ifndef LLMCAD_DEPTH_WIDE
 #define LLMCAD_DEPTH_WIDE 4
 #endif
+#ifndef LLMCAD_ROW_DEPTH  // most stages of a row-split tile (7B, 128 rows, us per pass: 6317 with 2, 5753 with 4, 5502 with 6, 5415 with 8; 10 is 1% behind 8)
+#define LLMCAD_ROW_DEPTH 8
+#endif
 #ifndef LLMCAD_TILE_BLOCKS_MB8
 #define LLMCAD_TILE_BLOCKS_MB8 4
 #endif
@@ -348,6 +351,48 @@ __device__ __forceinline__ TileIn tile_in(KParams& p, int step, int l) {
   return t;
 }
 
+// Block nb of a step's nb_total, dealt out in G contiguous runs: run w starts at
+// floor(w nb_total / G).  (32 bits hold the product: w < 1024, fewer than 2^21
+// blocks.  gshift: log2 G, or -1; a division costs a wave some 30 instructions,
+// in 64 bits 140, and there are several per phase before its first load.)
+__device__ __forceinline__ int run_start(KParams& p, int w, int nb_total) {
+  const uint32_t x = (uint32_t)w * (uint32_t)nb_total;
+  return wave_uniform((int)(p.gshift >= 0 ? x >> p.gshift : x / (uint32_t)p.G));
+}
+
+// log2 of the 16-column blocks per head (Dh 64 or 128).
+__device__ __forceinline__ int head_shift(KParams& p) { return p.Dh == 128 ? 3 : 2; }
+
+// The inputs of a tile's epilogue (written two or more phases ago) straight to
+// LDS: per (block, row block) the residual rows or the rotary table, then each
+// block's gains; waves [w0, kWaves) take them in turn.  A wait for those waves'
+// loads and a workgroup barrier publish them.
+template <int MB>
+__device__ __forceinline__ void epilogue_inputs(KParams& p, const TileIn& io, int step, int nb0, int cw, char* epi,
+                                                int w0) {
+  const int wave = wave_index(), lane = threadIdx.x & 63;
+  if (wave < w0 || (!io.resid && step != STEP_QKV)) return;
+  // residual rows 16 rb + l / 4, columns 16 nb + 4 (l % 4) .. + 3; (cos, sin)
+  // of rows 16 rb + l / 4, pairs 8 t + 2 (l % 4), + 1, t the block's place in
+  // its head
+  const int lr = lane >> 2, lc = 4 * (lane & 3);
+  const int tmask = (1 << head_shift(p)) - 1;
+#pragma unroll 1
+  for (int u = wave - w0; u < cw * MB; u += kWaves - w0) {
+    const int nb = nb0 + u / MB, row = 16 * (u % MB) + lr;
+    const float* src = (const float*)p.zero + lane * 4;
+    if (io.resid)
+      src = io.x_in + (size_t)row * p.d + kNB * nb + lc;
+    else if (nb < 2 * p.d_nb)
+      src = p.rope + (size_t)row * p.Dh + 16 * (nb & tmask) + lc;
+    dma16(src, epi + (size_t)u * 1024);
+  }
+  if (io.resid)
+#pragma unroll 1
+    for (int c = wave - w0; c < cw; c += kWaves - w0)
+      dma16(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1), epi + (size_t)(cw * MB + c) * 1024);
+}
+
 // Register stages per wave: at most ~160 VGPRs of them, and few -- 8 for
 // one-block tiles, 4 for wider ones.  The bytes in flight across a barrier
 // come mostly from the stages copied to LDS before it; a deeper register
@@ -401,7 +446,6 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   // same reason every load of a tile is unconditional: inputs a step does
   // not have are read from the zero line too.
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
-  const f32x4* zero4 = (const f32x4*)p.zero + lane;
   bf16x8 bw[D][C];
   bf16x8 ba[D][MB];
   // The first P stages of the wave's weights are copied into LDS before the
@@ -430,38 +474,13 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   const int ns0 = (ks + kWaves - 1) / kWaves;
   const int P0 = wave_uniform(wait_phase >= 0 ? (ns0 / D * D < pcap ? ns0 / D * D : pcap) : 0);
   // Epilogue inputs (residual stream or rotary table, and the next norm's
-  // gains; written two or more phases ago, so they need no barrier), by the
-  // last wave before the barrier: per (block, row block) unit 16 B per lane,
-  // then each block's gains, parked in LDS once they land -- before that
-  // wave's weight stages, so that the wait is for them alone (a wait behind
-  // a direct-to-LDS loop is a full drain).  After the barrier only the
-  // activations are then on the critical path.
-  constexpr int KU = C * MB;
-  constexpr int kEpiWave = kWaves - 1;
-  f32x4 sx[KU], sg[C];
-  if (wave == kEpiWave && epi_in) {
-    const bool resid = io.resid;
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int c = u / MB, rb = u % MB;
-      const int col0 = kNB * (nb0 + c);
-      const f32x4* src = zero4;
-      if (resid) {  // residual rows 16 rb + l / 4, columns col0 + 4 (l % 4) .. + 3
-        src = (const f32x4*)(io.x_in + (size_t)(16 * rb + (lane >> 2)) * p.d + col0 + 4 * (lane & 3));
-      } else if (step == STEP_QKV && col0 < 2 * p.d) {  // (cos, sin) of pairs 8 t + 2 (l % 4), + 1
-        const int t = (col0 % p.d % p.Dh) / kNB;
-        src = (const f32x4*)(p.rope + ((size_t)(16 * rb + (lane >> 2)) * (p.Dh / 2) + 8 * t + 2 * (lane & 3)) * 2);
-      }
-      sx[u] = ldg(opaque(src));
-    }
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      sg[c] = ldg(opaque(resid ? (const f32x4*)(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1)) : zero4));
-#pragma unroll
-    for (int u = 0; u < KU; ++u) lds_st<f32x4>(lds + epi_off(C, MB, SL) + (size_t)u * 1024 + lane * 16, sx[u]);
-#pragma unroll
-    for (int c = 0; c < C; ++c) lds_st<f32x4>(lds + epi_off(C, MB, SL) + (size_t)(C * MB + c) * 1024 + lane * 16, sg[c]);
-  }
+  // gains; written two or more phases ago, so they need no barrier), by waves
+  // 1-3 before the barrier, straight to LDS.  After the barrier only the
+  // activations are then on the critical path.  (A rolled loop: through
+  // registers, unrolled, with the block's place in its head found by two
+  // divisions per unit, it was up to half of a tile's 18 KiB of code, and the
+  // code a layer runs did not fit the 64 KiB instruction cache.)
+  if (epi_in) epilogue_inputs<MB>(p, io, step, nb0, C, lds + epi_off(C, MB, SL), 1);
   if (wave != 0) {
     if constexpr (PMAX > 0) {
       for (int i = 0; i < P; ++i)
@@ -494,6 +513,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   constexpr int SSQN = SSQR ? 8 : 1;
   f32x4 sr[SSQN];
   if constexpr (SSQR) {
+    const f32x4* zero4 = (const f32x4*)p.zero + lane;
     constexpr int QUADS = 4 * MB, CH = 256 / QUADS;
     const int q = threadIdx.x % QUADS, ch = threadIdx.x / QUADS;
     const int t0 = ch * p.d_nb / CH, t1 = (ch + 1) * p.d_nb / CH;
@@ -632,43 +652,48 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 // caps it at a few blocks at 64 and 128 rows, so a workgroup with more blocks
 // than that reads the whole activation matrix once per tile.  Here the waves
 // split the rows instead: wave w owns row blocks [w MB/4, (w + 1) MB/4) of
-// every k-step of the tile's C blocks, so a tile takes up to 8 blocks and its
+// every k-step of the tile's C blocks, so a tile takes up to 12 blocks and its
 // workgroup reads the activations once.  Per k-step wave w loads the weight
-// fragments of blocks w, w + 4 (a quarter of the tile) and its own row
-// blocks' activation fragments through its register pipeline, writes its
-// weight fragments to one of two LDS buffers, and after the workgroup's
-// barrier reads all C of them from there.  No partial sums cross waves: each
+// fragments of blocks w, w + 4, w + 8 (a quarter of the tile) and its own row
+// blocks' activation fragments through its register pipeline; its weight
+// fragments go to one of two LDS buffers two k-steps ahead of their use, and
+// every wave reads all C of them one ahead, so that behind the workgroup's
+// barrier per k-step no LDS access is waited for (7B gate/up at 128 rows: a
+// loop of 42 us with write, barrier, read and product in a row).  No partial sums cross waves: each
 // wave writes its rows' tiles to the one partial-tile slot.
+// k-steps [k0, k0 + kn) of the step's (all of them, or a split-K slice).
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KParams& pin, int step, int layer,
                                                                             int nb0, int wait_phase, char* lds,
-                                                                            int* lds_flag) {
+                                                                            int* lds_flag, int k0, int kn,
+                                                                            int epi_in) {
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
   nb0 = wave_uniform(nb0);
   wait_phase = wave_uniform(wait_phase);
+  k0 = wave_uniform(k0);
+  const int ks = wave_uniform(kn);
+  epi_in = wave_uniform(epi_in);
   const TileIn io = tile_in(p, step, layer);
   const int wave = wave_index(), lane = threadIdx.x & 63;
   constexpr int RB = MB / kWaves;              // row blocks per wave
   constexpr int NW = (C + kWaves - 1) / kWaves;  // weight fragments per wave per k-step
   static_assert(RB >= 1 && RB * kWaves == MB, "row-split tiles need 4 or 8 row blocks");
   constexpr int DR = LLMCAD_STAGE_REGS / (NW + RB);
-  constexpr int D = DR < 2 ? 2 : DR > 8 ? 8 : DR;
-  const int ks = wave_uniform(io.ks);
-  const size_t cstride = (size_t)ks * 64;
-  const bf16x8* at = io.a + (size_t)(wave * RB) * 64 + lane;
+  constexpr int D = DR < 4 ? 2 : DR > LLMCAD_ROW_DEPTH ? LLMCAD_ROW_DEPTH : DR / 2 * 2;
+  const size_t cstride = (size_t)io.ks * 64;
+  const bf16x8* at = io.a + ((size_t)k0 * MB + wave * RB) * 64 + lane;
+  const bf16x8* wt = io.w + ((size_t)(nb0 + wave) * io.ks + k0) * 64 + lane;
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
-  const f32x4* zero4 = (const f32x4*)p.zero + lane;
   bf16x8 bw[D][NW];
   bf16x8 ba[D][RB];
   // this wave's weight fragments: blocks wave + 4 j (j < NW) of the tile
   auto load_w = [&](int slot, int i) {  // k-step i, or the zero line past the last
 #pragma unroll
     for (int j = 0; j < NW; ++j) {
-      const int c = wave + kWaves * j;
-      const bool live = i < ks && c < C;
-      bw[slot][j] = ldg_nt(opaque(live ? io.w + ((size_t)(nb0 + c) * ks + i) * 64 + lane : zero));
+      const bool live = i < ks && wave + kWaves * j < C;
+      bw[slot][j] = ldg_nt(opaque(live ? wt + (size_t)(kWaves * j) * cstride + (size_t)i * 64 : zero));
     }
   };
   auto load_a = [&](int slot, int i) {
@@ -676,7 +701,15 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
 #pragma unroll
     for (int r = 0; r < RB; ++r) ba[slot][r] = ldg(opaque(live ? at + ((size_t)i * MB + r) * 64 : zero));
   };
-  char* wbuf = lds;  // two buffers of C KiB: k-step i's fragments in buffer i % 2, block c at c KiB
+  // two LDS buffers of C KiB: k-step i's fragments in buffer i % 2, block c at c KiB
+  auto share_w = [&](int slot, int i) {
+    char* buf = lds + (size_t)(i & 1) * C * 1024;
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      const int c = wave + kWaves * j;
+      if (c < C) lds_st<bf16x8>(buf + (size_t)c * 1024 + lane * 16, bw[slot][j]);
+    }
+  };
   // Waves 1-3 start their weight stages before the barrier; wave 0 polls it
   // with no load in flight (a poll waits for every older load of its wave).
   if (wave != 0) {
@@ -704,25 +737,33 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
   for (int r = 0; r < RB; ++r)
 #pragma unroll
     for (int c = 0; c < C; ++c) acc[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // one k-step from register stage u: share the weights, multiply, refill
+  bf16x8 b[2][C];  // k-step i's weights in b[i % 2]
+  auto read_w = [&](int i, int par) {
+    const char* buf = lds + (size_t)par * C * 1024;
+#pragma unroll
+    for (int c = 0; c < C; ++c) b[par][c] = lds_ld<bf16x8>(buf + (size_t)c * 1024 + lane * 16);
+  };
+  share_w(0, 0);
+  share_w(1, 1);
+  lds_barrier();
+  read_w(0, 0);
+  lds_barrier();
+  // k-step i from register stage u (i and u of one parity): read the next
+  // one's weights, put those of the one after it into the buffer this one's
+  // came from (every wave has read them), multiply, refill.  (Past the last
+  // k-step: zeros, or stale stages that nothing uses.)
   auto kstep = [&](int i, int u, bool refill) {
-    char* buf = wbuf + (size_t)(i & 1) * C * 1024;
+    read_w(i + 1, (u + 1) & 1);
+    share_w((u + 2) % D, u & 1);
 #pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int c = wave + kWaves * j;
-      if (c < C) lds_st<bf16x8>(buf + (size_t)c * 1024 + lane * 16, bw[u][j]);
-    }
-    lds_barrier();  // (the other buffer's readers are past the previous barrier)
+    for (int c = 0; c < C; ++c)
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const bf16x8 b = lds_ld<bf16x8>(buf + (size_t)c * 1024 + lane * 16);
-#pragma unroll
-      for (int r = 0; r < RB; ++r) acc[r][c] = mfma16x16x32(b, ba[u][r], acc[r][c]);
-    }
+      for (int r = 0; r < RB; ++r) acc[r][c] = mfma16x16x32(b[u & 1][c], ba[u][r], acc[r][c]);
     if (refill) {
       load_w(u, i + D);
       load_a(u, i + D);
     }
+    lds_barrier();
   };
   int i = 0;
   for (; i + D < ks; i += D) {
@@ -732,42 +773,24 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
 #pragma unroll
   for (int u = 0; u < D; ++u)
     if (i + u < ks) kstep(i + u, u, false);
-  lds_barrier();  // (every wave is done with the weight buffers)
   // this wave's rows -> the one slot: unit (block c, row block rb) at (c MB + rb) KiB
 #pragma unroll
   for (int c = 0; c < C; ++c)
 #pragma unroll
     for (int r = 0; r < RB; ++r)
       lds_st<f32x4>(lds + tw_off() + ((size_t)(c * MB + wave * RB + r) * 64 + lane) * 16, acc[r][c]);
-  // epilogue inputs (written two or more phases ago): per (block, row block)
-  // the residual rows or the rotary table, then each block's gains
-  char* epi = lds + epi_off(C, MB, 1);
-  const bool resid = io.resid;
-  for (int u = wave; u < C * MB; u += kWaves) {
-    const int c = u / MB, rb = u % MB;
-    const int col0 = kNB * (nb0 + c);
-    const f32x4* src = zero4;
-    if (resid) {
-      src = (const f32x4*)(io.x_in + (size_t)(16 * rb + (lane >> 2)) * p.d + col0 + 4 * (lane & 3));
-    } else if (step == STEP_QKV && col0 < 2 * p.d) {
-      const int t = (col0 % p.d % p.Dh) / kNB;
-      src = (const f32x4*)(p.rope + ((size_t)(16 * rb + (lane >> 2)) * (p.Dh / 2) + 8 * t + 2 * (lane & 3)) * 2);
-    }
-    lds_st<f32x4>(epi + (size_t)u * 1024 + lane * 16, ldg(opaque(src)));
-  }
-  for (int c = wave; c < C; c += kWaves)
-    lds_st<f32x4>(epi + (size_t)(C * MB + c) * 1024 + lane * 16,
-                  ldg(opaque(resid ? (const f32x4*)(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1)) : zero4)));
+  if (epi_in) epilogue_inputs<MB>(p, io, step, nb0, C, lds + epi_off(C, MB, 1), 0);
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   return true;
 }
 
 template <int MB, int C>
-__device__ __forceinline__ bool tile_dispatch_rows(int cw, KParams& p, int step, int layer, int nb0,
-                                                   int wait_phase, char* lds, int* flag) {
+__device__ __forceinline__ bool tile_dispatch_rows(int cw, KParams& p, int step, int layer, int nb0, int wait_phase,
+                                                   char* lds, int* flag, int k0, int kn, int epi_in) {
   if constexpr (C >= 1) {
-    if (cw == C) return tile_compute_rows<MB, C>(p, step, layer, nb0, wait_phase, lds, flag);
-    return tile_dispatch_rows<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, flag);
+    if (cw == C) return tile_compute_rows<MB, C>(p, step, layer, nb0, wait_phase, lds, flag, k0, kn, epi_in);
+    return tile_dispatch_rows<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, flag, k0, kn, epi_in);
   } else {
     return false;
   }
@@ -796,12 +819,14 @@ __device__ __forceinline__ bf16x8 q4_operand(uint32_t w, uint32_t mask, uint32_t
 __host__ __device__ constexpr int q4_kways(int MB) { return MB >= 8 ? 2 : 4; }
 
 // Widest 4-bit tile: the partial tiles and the epilogue inputs (which the
-// gate/up step does not have) fit the LDS region.
+// gate/up step does not have) fit the LDS region.  (Gate/up tiles of 8 blocks
+// at 64 rows would too, but take nearly every accumulation register: whatever
+// calls any tile of that pass then keeps its own values in scratch memory, and
+// the bf16 7B pass over 41 nodes, which runs no 4-bit tile, took 4% longer.)
 template <int MB, int EPI>
 constexpr int q4_tile_blocks() {
   if (MB <= 2) return 8;
-  if (EPI == EPI_SWIGLU) return MB == 4 ? 8 : 7;
-  return MB == 4 ? 6 : 5;
+  return MB == 4 ? 6 : EPI == EPI_SWIGLU ? 6 : 5;
 }
 
 // 4-bit tile: blocks [nb0, nb0 + C) of a layer step over its scale groups
@@ -901,24 +926,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   // first P groups of every wave, straight to LDS; then this wave's next D
   // groups into registers.
   if (wave != 0) {
-    if (epi) {
-      char* eb = lds + epi_off(C, MB, KW);
-      for (int u = wave - 1; u < C * MB; u += kWaves - 1) {
-        const int c = u / MB, rb = u % MB;
-        const int col0 = kNB * (nb0 + c);
-        const char* src = p.zero + lane * 16;
-        if (io.resid) {  // residual rows 16 rb + l / 4, columns col0 + 4 (l % 4) .. + 3
-          src = (const char*)(io.x_in + (size_t)(16 * rb + (lane >> 2)) * p.d + col0 + 4 * (lane & 3));
-        } else if (col0 < 2 * p.d) {  // (cos, sin) of pairs 8 t + 2 (l % 4), + 1
-          const int t = (col0 % p.d % p.Dh) / kNB;
-          src = (const char*)(p.rope + ((size_t)(16 * rb + (lane >> 2)) * (p.Dh / 2) + 8 * t + 2 * (lane & 3)) * 2);
-        }
-        dma16(src, eb + (size_t)u * 1024);
-      }
-      if (io.resid)
-        for (int c = wave - 1; c < C; c += kWaves - 1)
-          dma16(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1), eb + (size_t)(C * MB + c) * 1024);
-    }
+    if (epi) epilogue_inputs<MB>(p, io, step, nb0, C, lds + epi_off(C, MB, KW), 1);
     const int sbytes = P * KW * 32;  // of one block's scales
     for (int u = wave - 1; u < sck; u += kWaves - 1) {
       const int c = u / (sck / C), o = (u % (sck / C)) * 1024 + lane * 16;
@@ -1183,11 +1191,11 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
   const char* epi = lds + epi_off(cw, MB, nsum);
   const int col = kNB * nb + 4 * g;
   if constexpr (EPI == EPI_QKV) {
-    const int d = p.d, dh = p.Dh;
-    if (kNB * nb < 2 * d) {
+    const int dh = p.Dh, hs = head_shift(p);
+    if (nb < 2 * p.d_nb) {
       // q or k: this block holds dims [8t, 8t+8) (lanes < 32) and their
       // rotary partners + Dh/2 (lanes >= 32) of one head.
-      const int part = (kNB * nb) / d, cq = (kNB * nb) % d, hh = cq / dh, t = (cq % dh) / kNB;
+      const int part = nb < p.d_nb ? 0 : 1, nq = nb - part * p.d_nb, hh = nq >> hs, t = nq & ((1 << hs) - 1);
       const int dim = 8 * t + 4 * (g & 1) + (g < 2 ? 0 : dh / 2);
       const char* csu = epi + (size_t)unit * 1024 + (size_t)(li * 8 + 4 * (g & 1)) * 8;
       const f32x4 cs01 = lds_ld<f32x4>(csu), cs23 = lds_ld<f32x4>(csu + 16);
@@ -1200,14 +1208,14 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
         o[i] = g < 2 ? lo * cs[i] - hi * sn[i] : hi * cs[i] + lo * sn[i];
       }
       if (r < p.n) {
-        bf16* dst = part == 0 ? io.q + hh * dh + (size_t)r * d
+        bf16* dst = part == 0 ? io.q + hh * dh + (size_t)r * p.d
                               : io.kc + ((size_t)hh * p.cap + p.prefix_len + p.m0 + r) * dh;
         st_coherent_bf4(dst + dim, o);
       }
     } else {
       // v: the cache holds V transposed per head ([Dh][cap]); the 16 lanes of
       // a quarter wave hold 16 consecutive slots of each of its four dims
-      const int cv = col - 2 * d, hh = cv / dh, dim = cv % dh;
+      const int nv = nb - 2 * p.d_nb, hh = nv >> hs, dim = kNB * (nv & ((1 << hs) - 1)) + 4 * g;
       bf16* vcol = io.vc + ((size_t)hh * dh + dim) * p.cap + p.prefix_len + p.m0 + r;
       if (r < p.n) {
 #pragma unroll
@@ -1652,13 +1660,13 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
   const int nbk = sp.nblocks, ks = sp.ksteps;
   const int vw = virtual_wg(G);
   const int g = vw / S, sl = vw % S;
-  const int glo = wave_uniform((int)((long)g * nbk / NG));
-  const int ghi = wave_uniform((int)((long)(g + 1) * nbk / NG));
+  const int glo = run_start(p, g * S, nbk);  // (group g of G / S: floor(g nbk / (G / S)))
+  const int ghi = run_start(p, (g + 1) * S, nbk);
   const int bstride = (nbk + NG - 1) / NG;  // partial-tile slots per workgroup, in blocks
   const int k0 = sl * ks / S, k1 = (sl + 1) * ks / S;
   const int wave = wave_index(), lane = threadIdx.x & 63;
   constexpr int U = MB * 256;  // floats of one block's partial tiles
-  int* cnt = p.grp_cnt + (step == STEP_DOWN ? kPassMaxGrid / 2 : 0) + g;
+  int* cnt = p.grp_cnt + step * kSplitGroups + g;
   if (glo >= ghi) {  // (no blocks: the host splits only steps with a block per group)
     trace_mark(sy, phase, 0);
     if (!grid_wait(sy, phase, G)) return false;
@@ -1687,8 +1695,10 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
     return true;
   }
   const TileIn io = tile_in(p, step, layer);
-  for (int c0 = olo; c0 < ohi; c0 += CM) {
-    const int cw = wave_uniform(ohi - c0 < CM ? ohi - c0 : CM);
+  // (as many at once as the S partial tiles and the epilogue inputs of fit the LDS)
+  const int cfit = kGemmLdsBytes / 1024 / ((S + 1) * MB + 1), cf = wave_uniform(cfit < CM ? cfit : CM);
+  for (int c0 = olo; c0 < ohi; c0 += cf) {
+    const int cw = wave_uniform(ohi - c0 < cf ? ohi - c0 : cf);
     char* epi = lds + epi_off(cw, MB, S);
     // epilogue inputs (written two or more phases ago): the residual rows of
     // each unit and the next norm's gains, straight to LDS, before the wait
@@ -1716,10 +1726,120 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
   return true;
 }
 
+// A split-K phase of a 128-row pass with row-split tiles: each workgroup of a
+// group computes all the group's blocks (at most kSplitTile, one tile) over its
+// slice of the k-steps, stores the partial tiles of the blocks the others
+// finish, and adds theirs, in slice order, to its own for the blocks it
+// finishes itself.  It pays because a CU's loads are served in order, whoever
+// issues them and wherever they land: mixed with a stream from HBM, the
+// activations (L2 hits) come at the stream's latency, about 25 bytes per clock
+// and CU for both together, against 52 for L2 hits alone.  What counts at 128
+// rows is then the bytes a CU loads: at the 7B shape QKV 1417 KiB of
+// activations and weights, 953 with S = 2 and the exchange; O 1152, 430 with
+// S = 4; down 3168, 1760 with S = 2, 1100 with S = 4 (loops of 23.6 -> 18.9 us,
+// and 25.5 -> 20.1 us for down in fours instead of pairs).
+constexpr int kSplitTile = 12;
+
+// Adds the other slices' partial tiles (slice t's from src + t stride floats,
+// unit u at + 256 u) to this workgroup's own, slice sl's, in LDS, in slice
+// order; a batch of units' loads in one round trip.
+template <int S>
+__device__ __forceinline__ void split_gather(const float* src, size_t stride, int sl, char* own, int units) {
+  const int lane = threadIdx.x & 63;
+  constexpr int NB = S == 2 ? 8 : S == 4 ? 4 : 2;
+  for (int u0 = wave_index(); u0 < units; u0 += kWaves * NB) {
+    f32x4 o[NB][S - 1];  // the slices other than sl, in order
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int u = u0 + kWaves * k < units ? u0 + kWaves * k : u0;
+#pragma unroll
+      for (int t = 0; t < S - 1; ++t) {
+        const float* q = src + (size_t)(t < sl ? t : t + 1) * stride + (size_t)u * 256;
+        const float2 x = ld_coherent2(q), y = ld_coherent2(q + 2);
+        o[k][t] = f32x4{x.x, x.y, y.x, y.y};
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int u = u0 + kWaves * k;
+      if (u >= units) break;
+      char* at = own + ((size_t)u * 64 + lane) * 16;
+      const f32x4 self = lds_ld<f32x4>(at);
+      f32x4 sum = sl == 0 ? self : o[k][0];
+#pragma unroll
+      for (int t = 1; t < S; ++t) sum += t == sl ? self : t < sl ? o[k][t < S - 1 ? t : 0] : o[k][t - 1];
+      lds_st<f32x4>(at, sum);
+    }
+  }
+}
+
+template <int MB, int EPI>
+__device__ __attribute__((noinline, not_tail_called)) bool split_rows_phase(KParams& pin, int step, int layer,
+                                                                           int phase, char* lds, GemmLds& gl,
+                                                                           int* lds_flag) {
+  KParams& p = uniform_params(pin);
+  step = wave_uniform(step);
+  layer = wave_uniform(layer);
+  phase = wave_uniform(phase);
+  const Sync sy = make_sync(p, lds_flag);
+  const StepPlan& sp = p.step[step];
+  const int S = wave_uniform(sp.split), G = p.G, NG = G / S;
+  const int nbk = sp.nblocks, ks = sp.ksteps;
+  const int vw = virtual_wg(G);
+  const int g = vw / S, sl = wave_uniform(vw % S);
+  const int glo = run_start(p, g * S, nbk);  // (group g of G / S: floor(g nbk / (G / S)))
+  const int ghi = run_start(p, (g + 1) * S, nbk);
+  const int cw = ghi - glo;                 // 1 .. kSplitTile (the host's choice of S)
+  const int bstride = (nbk + NG - 1) / NG;  // partial-tile slots per workgroup, in blocks
+  const int k0 = sl * ks / S, k1 = (sl + 1) * ks / S;
+  const int wave = wave_index(), lane = threadIdx.x & 63;
+  constexpr int U = MB * 256;  // floats of one block's partial tiles
+  int* cnt = p.grp_cnt + step * kSplitGroups + g;
+  if (!tile_dispatch_rows<MB, kSplitTile>(cw, p, step, layer, glo, phase, lds, lds_flag, k0, k1 - k0, 0)) return false;
+  trace_mark(sy, phase, 4);
+  const int olo = wave_uniform(sl * cw / S), ohi = wave_uniform((sl + 1) * cw / S);  // the blocks it finishes
+  float* mine = p.part + (size_t)vw * bstride * U;
+  for (int u = wave; u < cw * MB; u += kWaves) {
+    if (u >= olo * MB && u < ohi * MB) continue;
+    const f32x4 s = lds_ld<f32x4>(lds + tw_off() + ((size_t)u * 64 + lane) * 16);
+    float* q = mine + ((size_t)u * 64 + lane) * 4;
+    st_coherent2(q, s[0], s[1]);
+    st_coherent2(q + 2, s[2], s[3]);
+  }
+  // This workgroup's partial tiles have completed; count its arrival.
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) atomic_add_dev(cnt, 1);
+  const int oc = ohi - olo;
+  if (oc == 0) {
+    trace_mark(sy, phase, 5);
+    return true;
+  }
+  // (its own blocks' partial tiles stay where they are; the epilogue inputs go
+  // after them, over blocks that have been stored)
+  char* own = lds + (size_t)olo * MB * 1024;
+  const TileIn io = tile_in(p, step, layer);
+  epilogue_inputs<MB>(p, io, step, glo + olo, oc, own + epi_off(oc, MB, 1), 0);
+  __builtin_amdgcn_s_waitcnt(0);
+  if (!counter_wait(sy, cnt, S * (layer + 1))) return false;
+  const float* src = p.part + (size_t)g * S * bstride * U + (size_t)olo * U + lane * 4;
+  if (S == 2)
+    split_gather<2>(src, (size_t)bstride * U, sl, own, oc * MB);
+  else if (S == 4)
+    split_gather<4>(src, (size_t)bstride * U, sl, own, oc * MB);
+  else
+    split_gather<8>(src, (size_t)bstride * U, sl, own, oc * MB);
+  __syncthreads();
+  finish_tile<MB, EPI>(p, step, layer, glo + olo, oc, own, gl, 1);
+  trace_mark(sy, phase, 5);
+  return true;
+}
+
 // One GEMM phase: this workgroup's run of blocks, in tiles over the full K
 // (K-split tiles of up to 8, 6 or 4 blocks at 32, 64 or 128 rows; row-split
 // tiles of up to 8 where a run exceeds one K-split tile at 64+ rows; 4-bit
-// tiles of up to 8, 6 or 5, gate/up's up to 8 or 7), each followed by its epilogue.  The LM head then
+// tiles of up to 8, 6 or 5, gate/up's up to 6 at 128 rows), each followed by its epilogue.  The LM head then
 // publishes the workgroup's argmax per row, and the last workgroup to do so
 // runs the accept walk.
 template <int MB, int EPI, int CM2 = 8>
@@ -1750,8 +1870,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
   const bool q4 = wave_uniform(sp.q4) != 0;
   const int nbk = sp.nblocks, G = p.G;
   const int vw = virtual_wg(G);
-  const int lo = wave_uniform((int)((long)vw * nbk / G));
-  const int hi = wave_uniform((int)((long)(vw + 1) * nbk / G));
+  const int lo = run_start(p, vw, nbk), hi = run_start(p, vw + 1, nbk);
   const bool rows = MB >= 4 && !q4 && wave_uniform(p.row_tiles) != 0 && hi - lo > CM;
   const int cm = q4 ? CMQ : rows ? CMR : CM;
   if constexpr (EPI == EPI_LOGITS) {
@@ -1775,7 +1894,8 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
     if constexpr (MB >= 4) {
       ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
                                               sp.ksteps, 1)
-           : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, lds, lds_flag)
+           : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, lds, lds_flag, 0,
+                                                sp.ksteps, 1)
                   : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
                                           sp.ksteps, 1);
     } else {
@@ -2354,8 +2474,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool final_norm_phase(KPar
   const float* x = p.x + (size_t)(2 * p.L) * p.Mp * p.d;
   const bf16* g = (const bf16*)(p.packed + p.o_final_norm);
   const int vw = virtual_wg(p.G);
-  const int lo = wave_uniform((int)((long)vw * p.d_nb / p.G));
-  const int hi = wave_uniform((int)((long)(vw + 1) * p.d_nb / p.G));
+  const int lo = run_start(p, vw, p.d_nb), hi = run_start(p, vw + 1, p.d_nb);
   for (int e = threadIdx.x; e < (hi - lo) * ROWS * (kNB / 2); e += kThreads) {
     const int pr = e % (kNB / 2), r = (e / (kNB / 2)) % ROWS, b = lo + e / ((kNB / 2) * ROWS);
     const int c = kNB * b + 2 * pr;
@@ -2397,24 +2516,38 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
   grid_arrive(sy, phase);
   ++phase;
 
+  // (one step's phase: split-K with row-split tiles at 128 rows, split-K with
+  // K-split tiles for the residual steps, or every block over the full K)
+  auto resid_phase = [&](int step, int l) {
+    if constexpr (MB == 8) {
+      if (p.step[step].split_rows) return split_rows_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag);
+    }
+    return p.step[step].split > 1 ? split_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag)
+                                  : gemm_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag);
+  };
   for (int l = 0; l < p.L && ok; ++l) {
-    ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
+    if (MB == 8 && p.step[STEP_QKV].split_rows) {
+      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
+    } else {
+      ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
+    }
     // (a pass that only fills the cache ends with the last layer's keys and values)
     if (!ok || (p.kv_only && l == p.L - 1)) break;
     grid_arrive(sy, phase++);
     ok = attn_phase<MB, DH>(p, l, phase, lds_raw, &flag);
     if (!ok) break;
     grid_arrive(sy, phase++);
-    ok = p.step[STEP_O].split > 1 ? split_phase<MB, EPI_RESID>(p, STEP_O, l, phase, lds_raw, gl, &flag)
-                                  : gemm_phase<MB, EPI_RESID>(p, STEP_O, l, phase, lds_raw, gl, &flag);
+    ok = resid_phase(STEP_O, l);
     if (!ok) break;
     grid_arrive(sy, phase++);
-    ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase, lds_raw, gl, &flag);
+    if (MB == 8 && p.step[STEP_GATE_UP].split_rows) {
+      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase, lds_raw, gl, &flag);
+    } else {
+      ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase, lds_raw, gl, &flag);
+    }
     if (!ok) break;
     grid_arrive(sy, phase++);
-    ok = p.step[STEP_DOWN].split > 1
-             ? split_phase<MB, EPI_RESID>(p, STEP_DOWN, l, phase, lds_raw, gl, &flag)
-             : gemm_phase<MB, EPI_RESID>(p, STEP_DOWN, l, phase, lds_raw, gl, &flag);
+    ok = resid_phase(STEP_DOWN, l);
     if (!ok) break;
     grid_arrive(sy, phase++);
   }
@@ -2427,11 +2560,10 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
   // group counters.
   if (arrive_last(p.exit_cnt, p.G, &flag)) {
     if (threadIdx.x < kBarSlots) st_coherent(p.bar + threadIdx.x * kBarStride, 0);
-    if (p.step[STEP_O].split > 1 || p.step[STEP_DOWN].split > 1)
-      for (int i = threadIdx.x; i < p.G / 2; i += kThreads) {
-        st_coherent(p.grp_cnt + i, 0);
-        st_coherent(p.grp_cnt + kPassMaxGrid / 2 + i, 0);
-      }
+    for (int step = 0; step < STEP_LM; ++step)
+      if (p.step[step].split > 1)
+        for (int i = threadIdx.x; i < p.G / p.step[step].split; i += kThreads)
+          st_coherent(p.grp_cnt + step * kSplitGroups + i, 0);
   }
 }
 
@@ -2507,6 +2639,11 @@ int pass_occupancy(int mb16, int dh, bool wide) {
       return 0;
   }
 #undef LLMCAD_OCC_CASE
+}
+
+bool split_rows_fits(int cw, int oc, bool epi) {
+  return cw <= kSplitTile && (cw - oc) * 8 * 1024 + (epi ? wl_off(oc, 8, 1) : epi_off(oc, 8, 1)) <= kGemmLdsBytes &&
+         epi_off(cw, 8, 1) <= kGemmLdsBytes;
 }
 
 size_t pass_lds_bytes(int mb16, int dh) {

@@ -191,6 +191,28 @@ def test_row_split_tiles(model, monkeypatch, tree):
         monkeypatch.delenv("LLMCAD_PASS_GRID")
 
 
+@pytest.mark.parametrize("grid,S", [(32, 2), (16, 2), (16, 4), (32, 8), (64, 8), (24, 4)])
+def test_split_k_row_tiles(model, monkeypatch, grid, S):
+    # Split-K with row-split tiles (128-row passes): every step of a layer in
+    # groups of S workgroups, each over a slice of the k-steps (with S = 8 some
+    # of one k-step or none), with groups of 1 to 12 blocks, shares of several
+    # blocks and of none; steps whose groups do not fit run as without it.  The oracle
+    # bar, other sums than the unsplit pass's, and the same bits twice.
+    parent = TREES["random_n128" if grid != 24 else "random_n77"]
+    tok = workloads.draw_tokens(len(parent), model.shape.vocab, seed=17)
+    monkeypatch.setenv("LLMCAD_PASS_GRID", str(grid))
+    names = ("QKV", "O", "GU", "DOWN")
+    for name in names:
+        monkeypatch.setenv(f"LLMCAD_SPLIT_{name}", "1")
+    base = _check_all(model, parent, tok, f"grid {grid} unsplit")
+    for name in names:
+        monkeypatch.setenv(f"LLMCAD_SPLIT_{name}", str(S))
+    split = _check_all(model, parent, tok, f"grid {grid} S {S}")
+    if model.shape.weight_bits == 16:
+        assert not np.array_equal(base, split), "the split-K path did not run"
+    np.testing.assert_array_equal(split, _run(model, parent, tok)[0])
+
+
 def _long_prefix_session(model, PL):
     """A session whose cache holds PL seeded random bf16 prefix keys/values
     (written straight into the cache) and the oracle's copies of them."""
