@@ -125,7 +125,6 @@ hipError_t launch_pass(int mb16, const PassParams& p, const TreeArgs& tree, hipS
 // row-split tile of a 128-row pass (epi: the step has epilogue inputs).
 bool split_rows_fits(int cw, int oc, bool epi);
 int pass_occupancy(int mb16, int dh, bool wide);  // resident workgroups per CU (0 if unavailable)
-size_t pass_lds_bytes(int mb16, int dh);
 
 
 }  // namespace llmcad

@@ -142,12 +142,27 @@ struct Sync {
   long long* trace;  // [phase][8] timestamps of this workgroup, or null
 };
 
-__device__ __forceinline__ Sync make_sync(KParams& p, int* lds_flag) {
+// LDS of a workgroup.  Every function finds it by itself, at addresses fixed when
+// the kernels are linked: handed down as pointers it cost each call between the
+// phases' functions six registers to keep (in scratch memory, as a callee may
+// use all others) and to reload, and every access an address of its own.
+constexpr int kGemmLdsBytes = 142 * 1024;
+// The GEMM tiles' region (the attention's prefetched steps and merge, too).
+__device__ __forceinline__ char* lds_region() {
+  __shared__ __attribute__((aligned(1024))) char region[kGemmLdsBytes];
+  return region;
+}
+__device__ __forceinline__ int* wait_flag() {
+  __shared__ int flag;
+  return &flag;
+}
+
+__device__ __forceinline__ Sync make_sync(KParams& p) {
   Sync s;
   s.bar = p.bar;
   s.status = p.status;
   s.limit = p.spin_limit;
-  s.lds_flag = lds_flag;
+  s.lds_flag = wait_flag();
   s.trace = p.trace != nullptr ? p.trace + (size_t)blockIdx.x * pass_phases(p.L) * 8 : nullptr;
   return s;
 }
@@ -245,7 +260,12 @@ struct GemmLds {
   int walk_len;
 };
 
-// LDS of a GEMM tile of cw blocks (dynamic shared memory), in KiB, with
+__device__ __forceinline__ GemmLds& gemm_lds() {
+  __shared__ GemmLds gl;
+  return gl;
+}
+
+// LDS of a GEMM tile of cw blocks (in lds_region()), in KiB, with
 // SL partial-tile slots:
 //   [0, SL cw MB)                the partial tiles, fp32 [SL][cw][MB][64 lanes][4]:
 //                                the four waves' (SL = 4), or two sums of
@@ -259,7 +279,6 @@ struct GemmLds {
 //                                (bf16, first 32 bytes)
 //   [(SL+1) cw MB + cw, 142)     the first weight stages of each wave, copied
 //                                before the phase's barrier
-constexpr int kGemmLdsBytes = 142 * 1024;
 __host__ __device__ constexpr int tw_off() { return 0; }
 __host__ __device__ constexpr int epi_off(int cw, int MB, int SL) { return SL * cw * MB * 1024; }
 __host__ __device__ constexpr int wl_off(int cw, int MB, int SL) { return ((SL + 1) * cw * MB + cw) * 1024; }
@@ -414,9 +433,10 @@ constexpr int tile_depth() {
 // in LDS.  False if a wait ran out.
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams& pin, int step, int layer,
-                                                                       int nb0, int wait_phase, char* lds,
-                                                                       GemmLds& gl, int* lds_flag, int k0,
-                                                                       int kn, int epi_in) {
+                                                                       int nb0, int wait_phase, int k0, int kn,
+                                                                       int epi_in) {
+  char* const lds = lds_region();
+  GemmLds& gl = gemm_lds();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
@@ -501,7 +521,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0) {
-    const Sync sy = make_sync(p, lds_flag);
+    const Sync sy = make_sync(p);
     trace_mark(sy, wait_phase, 0);
     if (!grid_wait(sy, wait_phase, p.G)) return false;
     trace_mark(sy, wait_phase, 1);
@@ -664,9 +684,9 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 // k-steps [k0, k0 + kn) of the step's (all of them, or a split-K slice).
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KParams& pin, int step, int layer,
-                                                                            int nb0, int wait_phase, char* lds,
-                                                                            int* lds_flag, int k0, int kn,
+                                                                            int nb0, int wait_phase, int k0, int kn,
                                                                             int epi_in) {
+  char* const lds = lds_region();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
@@ -718,7 +738,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0) {
-    const Sync sy = make_sync(p, lds_flag);
+    const Sync sy = make_sync(p);
     trace_mark(sy, wait_phase, 0);
     if (!grid_wait(sy, wait_phase, p.G)) return false;
     trace_mark(sy, wait_phase, 1);
@@ -787,10 +807,10 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
 
 template <int MB, int C>
 __device__ __forceinline__ bool tile_dispatch_rows(int cw, KParams& p, int step, int layer, int nb0, int wait_phase,
-                                                   char* lds, int* flag, int k0, int kn, int epi_in) {
+                                                   int k0, int kn, int epi_in) {
   if constexpr (C >= 1) {
-    if (cw == C) return tile_compute_rows<MB, C>(p, step, layer, nb0, wait_phase, lds, flag, k0, kn, epi_in);
-    return tile_dispatch_rows<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, flag, k0, kn, epi_in);
+    if (cw == C) return tile_compute_rows<MB, C>(p, step, layer, nb0, wait_phase, k0, kn, epi_in);
+    return tile_dispatch_rows<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, k0, kn, epi_in);
   } else {
     return false;
   }
@@ -847,9 +867,10 @@ constexpr int q4_tile_blocks() {
 // codes came through registers and each wave kept every row block).
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KParams& pin, int step, int layer,
-                                                                          int nb0, int wait_phase, char* lds,
-                                                                          GemmLds& gl, int* lds_flag, int k0, int kn,
+                                                                          int nb0, int wait_phase, int k0, int kn,
                                                                           int epi_in) {
+  char* const lds = lds_region();
+  GemmLds& gl = gemm_lds();
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   KParams& p = uniform_params(pin);
@@ -943,7 +964,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0) {
-    const Sync sy = make_sync(p, lds_flag);
+    const Sync sy = make_sync(p);
     trace_mark(sy, wait_phase, 0);
     if (!grid_wait(sy, wait_phase, p.G)) return false;
     trace_mark(sy, wait_phase, 1);
@@ -1075,10 +1096,10 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 
 template <int MB, int C>
 __device__ __forceinline__ bool tile_dispatch_q4(int cw, KParams& p, int step, int layer, int nb0, int wait_phase,
-                                                 char* lds, GemmLds& gl, int* flag, int k0, int kn, int epi_in) {
+                                                 int k0, int kn, int epi_in) {
   if constexpr (C >= 1) {
-    if (cw == C) return tile_compute_q4<MB, C>(p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
-    return tile_dispatch_q4<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
+    if (cw == C) return tile_compute_q4<MB, C>(p, step, layer, nb0, wait_phase, k0, kn, epi_in);
+    return tile_dispatch_q4<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, k0, kn, epi_in);
   } else {
     return false;
   }
@@ -1086,10 +1107,10 @@ __device__ __forceinline__ bool tile_dispatch_q4(int cw, KParams& p, int step, i
 
 template <int MB, int C>
 __device__ __forceinline__ bool tile_dispatch(int cw, KParams& p, int step, int layer, int nb0, int wait_phase,
-                                              char* lds, GemmLds& gl, int* flag, int k0, int kn, int epi_in) {
+                                              int k0, int kn, int epi_in) {
   if constexpr (C >= 1) {
-    if (cw == C) return tile_compute<MB, C>(p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
-    return tile_dispatch<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, lds, gl, flag, k0, kn, epi_in);
+    if (cw == C) return tile_compute<MB, C>(p, step, layer, nb0, wait_phase, k0, kn, epi_in);
+    return tile_dispatch<MB, C - 1>(cw, p, step, layer, nb0, wait_phase, k0, kn, epi_in);
   } else {
     return false;
   }
@@ -1106,7 +1127,8 @@ __device__ __forceinline__ float rope_inv_freq(int j, int Dh, float log2_theta) 
 // across the wave, then (gl.part_ss2) across the waves, in a fixed order.  (One
 // thread per row adding up to 64 chunks in turn: +0.2 us per epilogue.)
 template <int MB>
-__device__ __forceinline__ void chunk_scales(KParams& p, GemmLds& gl) {
+__device__ __forceinline__ void chunk_scales(KParams& p) {
+  GemmLds& gl = gemm_lds();
   constexpr int ROWS = 16 * MB, NP = ROWS < 64 ? kWaves : kThreads / ROWS;
   const int row = threadIdx.x % ROWS, part = threadIdx.x / ROWS;
   float t = 0.0f;
@@ -1132,7 +1154,8 @@ __device__ __forceinline__ void chunk_scales(KParams& p, GemmLds& gl) {
 
 // The same from a version's sums of squares ssq [d/16][Mp].
 template <int MB>
-__device__ __forceinline__ void row_rstd(KParams& p, const float* ssq, GemmLds& gl) {
+__device__ __forceinline__ void row_rstd(KParams& p, const float* ssq) {
+  GemmLds& gl = gemm_lds();
   // thread t: rows 4 q .. 4 q + 3 (q = t % (ROWS / 4)) of the 16-column blocks
   // of chunk t / (ROWS / 4); 16-byte loads, a batch of them in flight at once
   // (a chunk's 4096 columns in one batch at 128 rows)
@@ -1151,17 +1174,17 @@ __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq, GemmLds& 
   }
   *(f32x4*)&gl.part_ss[ch * ROWS + 4 * q] = ss;
   __syncthreads();
-  chunk_scales<MB>(p, gl);
+  chunk_scales<MB>(p);
 }
 
 // A norm step's row scales; when its tile held the sums of squares in
 // registers the chunk sums are in part_ss already.
 template <int MB>
-__device__ __forceinline__ void row_scales(KParams& p, const StepIo& io, GemmLds& gl) {
+__device__ __forceinline__ void row_scales(KParams& p, const StepIo& io) {
   if (MB <= 2 && p.ssq_regs)
-    chunk_scales<MB>(p, gl);
+    chunk_scales<MB>(p);
   else
-    row_rstd<MB>(p, io.ssq, gl);
+    row_rstd<MB>(p, io.ssq);
 }
 
 // Epilogue of one accumulator tile ("unit": block c of the tile x row block
@@ -1179,7 +1202,8 @@ __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io, GemmLds
 // Outputs are written with device-coherent stores.
 template <int MB, int EPI>
 __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, const char* lds, int cw, int c, int rb,
-                                              int nb, GemmLds& gl, int nsum) {
+                                              int nb, int nsum) {
+  GemmLds& gl = gemm_lds();
   const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int unit = c * MB + rb;
   f32x4 v = lds_ld<f32x4>(lds + tw_off() + ((size_t)unit * 64 + lane) * 16);
@@ -1311,7 +1335,8 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
 // reductions are interleaved, and reachability is found by pointer jumping
 // (ceil(log2 n) rounds over all nodes at once) instead of a serial walk.
 // (LDS hand-offs only: lds_barrier, which leaves the global stores in flight.)
-__device__ __forceinline__ void finish_walk(KParams& p, int entries, GemmLds& gl) {
+__device__ __forceinline__ void finish_walk(KParams& p, int entries) {
+  GemmLds& gl = gemm_lds();
   const int wave = wave_index(), lane = threadIdx.x & 63;
   const int n = p.n;
   // the tree (written by the first phase): one node per thread (n <= 128)
@@ -1442,9 +1467,10 @@ __device__ __forceinline__ void softmax_merge(float& m, float& s, int& ix, float
 // merged (one wave, in a fixed order), the stored logits row is scanned once
 // for every token whose probability exp(logit - max) / normaliser exceeds
 // the threshold, and the argmax and those tokens are written sorted by
-// probability, higher first (ties: lower token first).  `lds`: the GEMM
-// tiles' region, free once the phase's tiles are done.
-__device__ __attribute__((noinline, not_tail_called)) void finish_candidates(KParams& pin, int entries, char* lds) {
+// probability, higher first (ties: lower token first).  It works in the
+// GEMM tiles' region, free once the phase's tiles are done.
+__device__ __attribute__((noinline, not_tail_called)) void finish_candidates(KParams& pin, int entries) {
+  char* const lds = lds_region();
   KParams& p = uniform_params(pin);
   const int wave = wave_index(), lane = threadIdx.x & 63;
   float* sm = (float*)lds;       // the row's max and normaliser
@@ -1542,7 +1568,9 @@ __device__ __attribute__((noinline, not_tail_called)) void finish_candidates(KPa
 // registers are allocated apart from the streaming loop's.
 template <int MB, int EPI>
 __device__ __attribute__((noinline, not_tail_called)) void finish_tile(KParams& pin, int step, int layer, int nb0,
-                                                                      int cw, char* lds, GemmLds& gl, int nsum) {
+                                                                      int cw, int nsum, int off) {
+  char* const lds = lds_region() + (size_t)wave_uniform(off) * 1024;  // (the tile at `off` KiB of the region)
+  GemmLds& gl = gemm_lds();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
@@ -1550,11 +1578,11 @@ __device__ __attribute__((noinline, not_tail_called)) void finish_tile(KParams& 
   cw = wave_uniform(cw);
   nsum = wave_uniform(nsum);
   const StepIo io = step_io<EPI>(p, step, layer);
-  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) row_scales<MB>(p, io, gl);
+  if constexpr (EPI == EPI_QKV || EPI == EPI_SWIGLU) row_scales<MB>(p, io);
   const int units = cw * MB;
   for (int u = wave_index(); u < units; u += kWaves) {
     const int c = u / MB, rb = u % MB;
-    epilogue_unit<MB, EPI>(p, io, lds, cw, c, rb, nb0 + c, gl, nsum);
+    epilogue_unit<MB, EPI>(p, io, lds, cw, c, rb, nb0 + c, nsum);
   }
   if constexpr (EPI == EPI_LOGITS) {
     __syncthreads();
@@ -1646,14 +1674,14 @@ __device__ __forceinline__ bool counter_wait(const Sync& s, const int* cnt, int 
 // for the pass), so the counter reaches S (layer + 1) exactly when the group
 // has arrived in this layer.
 template <int MB, int EPI>
-__device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& pin, int step, int layer,
-                                                                      int phase, char* lds, GemmLds& gl,
-                                                                      int* lds_flag) {
+__device__ __forceinline__ bool split_phase(KParams& pin, int step, int layer,
+                                                                      int phase) {
+  char* const lds = lds_region();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
   phase = wave_uniform(phase);
-  const Sync sy = make_sync(p, lds_flag);
+  const Sync sy = make_sync(p);
   const StepPlan& sp = p.step[step];
   constexpr int CM = MB <= 2 ? 8 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
   const int S = wave_uniform(sp.split), G = p.G, NG = G / S;
@@ -1677,7 +1705,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
   for (int b0 = glo; b0 < ghi; b0 += CM) {
     const int cw = ghi - b0 < CM ? ghi - b0 : CM;
     const bool first = b0 == glo;
-    if (!tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, k0, k1 - k0, 0))
+    if (!tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, k0, k1 - k0, 0))
       return false;
     if (first) trace_mark(sy, phase, 4);
     split_store<MB>(lds, cw, mine + (size_t)(b0 - glo) * U);
@@ -1720,7 +1748,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_phase(KParams& 
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    finish_tile<MB, EPI>(p, step, layer, c0, cw, lds, gl, S);
+    finish_tile<MB, EPI>(p, step, layer, c0, cw, S, 0);
   }
   trace_mark(sy, phase, 5);
   return true;
@@ -1774,14 +1802,14 @@ __device__ __forceinline__ void split_gather(const float* src, size_t stride, in
 }
 
 template <int MB, int EPI>
-__device__ __attribute__((noinline, not_tail_called)) bool split_rows_phase(KParams& pin, int step, int layer,
-                                                                           int phase, char* lds, GemmLds& gl,
-                                                                           int* lds_flag) {
+__device__ __forceinline__ bool split_rows_phase(KParams& pin, int step, int layer,
+                                                                           int phase) {
+  char* const lds = lds_region();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
   phase = wave_uniform(phase);
-  const Sync sy = make_sync(p, lds_flag);
+  const Sync sy = make_sync(p);
   const StepPlan& sp = p.step[step];
   const int S = wave_uniform(sp.split), G = p.G, NG = G / S;
   const int nbk = sp.nblocks, ks = sp.ksteps;
@@ -1795,7 +1823,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_rows_phase(KPar
   const int wave = wave_index(), lane = threadIdx.x & 63;
   constexpr int U = MB * 256;  // floats of one block's partial tiles
   int* cnt = p.grp_cnt + step * kSplitGroups + g;
-  if (!tile_dispatch_rows<MB, kSplitTile>(cw, p, step, layer, glo, phase, lds, lds_flag, k0, k1 - k0, 0)) return false;
+  if (!tile_dispatch_rows<MB, kSplitTile>(cw, p, step, layer, glo, phase, k0, k1 - k0, 0)) return false;
   trace_mark(sy, phase, 4);
   const int olo = wave_uniform(sl * cw / S), ohi = wave_uniform((sl + 1) * cw / S);  // the blocks it finishes
   float* mine = p.part + (size_t)vw * bstride * U;
@@ -1831,7 +1859,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_rows_phase(KPar
   else
     split_gather<8>(src, (size_t)bstride * U, sl, own, oc * MB);
   __syncthreads();
-  finish_tile<MB, EPI>(p, step, layer, glo + olo, oc, own, gl, 1);
+  finish_tile<MB, EPI>(p, step, layer, glo + olo, oc, 1, olo * MB);
   trace_mark(sy, phase, 5);
   return true;
 }
@@ -1843,14 +1871,13 @@ __device__ __attribute__((noinline, not_tail_called)) bool split_rows_phase(KPar
 // publishes the workgroup's argmax per row, and the last workgroup to do so
 // runs the accept walk.
 template <int MB, int EPI, int CM2 = 8>
-__device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& pin, int step, int layer,
-                                                                     int phase, char* lds, GemmLds& gl,
-                                                                     int* lds_flag) {
+__device__ __forceinline__ bool gemm_phase(KParams& pin, int step, int layer,
+                                                                     int phase) {
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
   phase = wave_uniform(phase);
-  const Sync sy = make_sync(p, lds_flag);
+  const Sync sy = make_sync(p);
   const StepPlan& sp = p.step[step];
   // (CM2: 8, or 9 for a step marked wide; the LM head keeps 8, its per-block
   // argmax slots)
@@ -1874,6 +1901,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
   const bool rows = MB >= 4 && !q4 && wave_uniform(p.row_tiles) != 0 && hi - lo > CM;
   const int cm = q4 ? CMQ : rows ? CMR : CM;
   if constexpr (EPI == EPI_LOGITS) {
+    GemmLds& gl = gemm_lds();
     for (int r = threadIdx.x; r < 16 * MB; r += kThreads) {
       gl.best_v[r] = -INFINITY;
       gl.best_i[r] = 0x7fffffff;
@@ -1892,37 +1920,33 @@ __device__ __attribute__((noinline, not_tail_called)) bool gemm_phase(KParams& p
     const bool first = b0 == lo;
     bool ok;
     if constexpr (MB >= 4) {
-      ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
-                                              sp.ksteps, 1)
-           : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, lds, lds_flag, 0,
-                                                sp.ksteps, 1)
-                  : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
-                                          sp.ksteps, 1);
+      ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1)
+           : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1)
+                  : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1);
     } else {
-      ok = q4 ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
-                                          sp.ksteps, 1)
-              : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, lds, gl, lds_flag, 0,
-                                      sp.ksteps, 1);
+      ok = q4 ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1)
+              : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1);
     }
     if (!ok) return false;
     if (first) trace_mark(sy, phase, 4);
-    finish_tile<MB, EPI>(p, step, layer, b0, cw, lds, gl, q4 ? q4_kways(MB) : rows ? 1 : tile_slots(cw, MB));
+    finish_tile<MB, EPI>(p, step, layer, b0, cw, q4 ? q4_kways(MB) : rows ? 1 : tile_slots(cw, MB), 0);
   }
   trace_mark(sy, phase, 5);
   if constexpr (EPI == EPI_LOGITS) {
     __syncthreads();
+    GemmLds& gl = gemm_lds();
     for (int r = threadIdx.x; r < 16 * MB; r += kThreads) {
       st_coherent(&p.lm_val[(size_t)r * G + blockIdx.x], gl.best_v[r]);
       st_coherent(&p.lm_idx[(size_t)r * G + blockIdx.x], gl.best_i[r]);
       if (p.cand != nullptr) st_coherent(&p.lm_sum[(size_t)r * G + blockIdx.x], gl.best_s[r]);
     }
-    if (arrive_last(p.lm_cnt, G, lds_flag)) {
+    if (arrive_last(p.lm_cnt, G, wait_flag())) {
       if (p.m0 == 0) {
         trace_mark(sy, phase, 6);
-        finish_walk(p, G, gl);
+        finish_walk(p, G);
         trace_mark(sy, phase, 7);
       }
-      if (p.cand != nullptr) finish_candidates(p, G, lds);
+      if (p.cand != nullptr) finish_candidates(p, G);
     }
   }
   return true;
@@ -2111,10 +2135,10 @@ __device__ __forceinline__ void attn_compute(const AttnStep<DH>& R, const bf16x8
 // tree's split merges them with its own, in split order.  MB: 16-row blocks
 // of the pass.
 template <int MB, int DH>
-__device__ __attribute__((noinline, not_tail_called)) bool attn_phase(KParams& pin, int layer, int phase, char* lds,
-                                                                     int* lds_flag) {
+__device__ __attribute__((noinline, not_tail_called)) bool attn_phase(KParams& pin, int layer, int phase) {
+  char* const lds = lds_region();
   KParams& p = uniform_params(pin);
-  const Sync sy = make_sync(p, lds_flag);
+  const Sync sy = make_sync(p);
   layer = wave_uniform(layer);
   phase = wave_uniform(phase);
   using PF = AttnPrefetch<DH>;
@@ -2315,7 +2339,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool attn_phase(KParams& p
         st_coherent2(&p.attn_o[(sl * 16 + i) * DH + dd], u0[k], u1[k]);
         if (dd == 0) st_coherent2(&p.attn_ml[(sl * 16 + i) * 2], uM[k], uL[k]);
       }
-      merge = arrive_last(&p.head_cnt[rbi], KS, lds_flag);
+      merge = arrive_last(&p.head_cnt[rbi], KS, wait_flag());
       if (merge) trace_mark(sy, phase, 6);
     }
     if (merge) {
@@ -2440,17 +2464,13 @@ __device__ __forceinline__ void embed_phase(KParams& p, const TreeArgs& tree, in
 
 // ------------------------------------------------------------------ kernel
 
-// Dynamic LDS: the GEMM tiles' region (all LDS but the static part), which
-// the attention reuses for its prefetched steps and its merge.
 template <int DH>
-constexpr size_t dyn_lds_bytes() {
-  static_assert(AttnPrefetch<DH>::W0 >= 1 && AttnPrefetch<DH>::W23 >= 1 &&
-                    (size_t)(AttnPrefetch<DH>::W0 + 2 * AttnPrefetch<DH>::W23) * AttnPrefetch<DH>::STEP_BYTES <=
-                        kGemmLdsBytes,
-                "attention prefetch slots");
-  static_assert((size_t)kWaves * 16 * (DH + 2) * 4 <= kGemmLdsBytes, "attention merge");
-  return kGemmLdsBytes;
+constexpr bool attn_lds_fits() {  // the attention's prefetched steps and merge fit the region
+  using PF = AttnPrefetch<DH>;
+  return PF::W0 >= 1 && PF::W23 >= 1 && (size_t)(PF::W0 + 2 * PF::W23) * PF::STEP_BYTES <= kGemmLdsBytes &&
+         (size_t)kWaves * 16 * (DH + 2) * 4 <= kGemmLdsBytes;
 }
+static_assert(attn_lds_fits<64>() && attn_lds_fits<128>(), "attention in the GEMM tiles' region");
 
 // ------------------------------------------------------------------ final norm
 
@@ -2461,16 +2481,16 @@ constexpr size_t dyn_lds_bytes() {
 // model's rounding point.)  Workgroup w takes the 16-column blocks
 // [w d/16 / G, (w + 1) d/16 / G).
 template <int MB>
-__device__ __attribute__((noinline, not_tail_called)) bool final_norm_phase(KParams& pin, int phase, GemmLds& gl,
-                                                                           int* lds_flag) {
+__device__ __attribute__((noinline, not_tail_called)) bool final_norm_phase(KParams& pin, int phase) {
+  GemmLds& gl = gemm_lds();
   KParams& p = uniform_params(pin);
   phase = wave_uniform(phase);
-  const Sync sy = make_sync(p, lds_flag);
+  const Sync sy = make_sync(p);
   trace_mark(sy, phase, 0);
   if (!grid_wait(sy, phase, p.G)) return false;
   trace_mark(sy, phase, 1);
   constexpr int ROWS = 16 * MB;
-  row_rstd<MB>(p, p.ssq + (size_t)(2 * p.L) * p.d_nb * p.Mp, gl);
+  row_rstd<MB>(p, p.ssq + (size_t)(2 * p.L) * p.d_nb * p.Mp);
   const float* x = p.x + (size_t)(2 * p.L) * p.Mp * p.d;
   const bf16* g = (const bf16*)(p.packed + p.o_final_norm);
   const int vw = virtual_wg(p.G);
@@ -2492,17 +2512,14 @@ __device__ __attribute__((noinline, not_tail_called)) bool final_norm_phase(KPar
 // other kernels' code is unchanged by it).
 template <int MB, int DH, bool WIDE = false>
 __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_arg, const TreeArgs tree) {
-  extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
-  __shared__ GemmLds gl;
   __shared__ int par_s[128];
-  __shared__ int flag;
   // The parameter block is the first kernel argument: read it in place.
   KParams& p = *(KParams*)__builtin_amdgcn_kernarg_segment_ptr();
   if (p.magic != kPassMagic || p.G != p_arg.G || p.n != p_arg.n || p.Mp != 16 * MB) {
     if (threadIdx.x == 0 && blockIdx.x == 0) stg(p_arg.status, 3);
     return;  // (uniform over the grid: no workgroup reaches a barrier)
   }
-  const Sync sy = make_sync(p, &flag);
+  const Sync sy = make_sync(p);
   int phase = 0;
   bool ok = true;
 
@@ -2516,49 +2533,53 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
   grid_arrive(sy, phase);
   ++phase;
 
-  // (one step's phase: split-K with row-split tiles at 128 rows, split-K with
-  // K-split tiles for the residual steps, or every block over the full K)
-  auto resid_phase = [&](int step, int l) {
-    if constexpr (MB == 8) {
-      if (p.step[step].split_rows) return split_rows_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag);
-    }
-    return p.step[step].split > 1 ? split_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag)
-                                  : gemm_phase<MB, EPI_RESID>(p, step, l, phase, lds_raw, gl, &flag);
-  };
-  for (int l = 0; l < p.L && ok; ++l) {
-    if (MB == 8 && p.step[STEP_QKV].split_rows) {
-      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
+  // Half a layer per round: QKV, attention and O, then gate/up and down, so that
+  // the residual steps' code is there once.  The phases are part of this
+  // function, not functions of their own: one that calls the tiles, which use
+  // every register, saved its caller's values to scratch memory and fetched
+  // them back when it returned, 0.3 to 1.7 us per phase behind the weight
+  // stream's loads.
+  for (int s = 0; s < 2 * p.L && ok; ++s) {
+    const int l = s >> 1;
+    const bool ffn = (s & 1) != 0;
+    if (!ffn) {
+      if (MB == 8 && p.step[STEP_QKV].split_rows) {
+        if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase);
+      } else {
+        ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase);
+      }
+      // (a pass that only fills the cache ends with the last layer's keys and values)
+      if (!ok || (p.kv_only && l == p.L - 1)) break;
+      grid_arrive(sy, phase++);
+      ok = attn_phase<MB, DH>(p, l, phase);
+    } else if (MB == 8 && p.step[STEP_GATE_UP].split_rows) {
+      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase);
     } else {
-      ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase, lds_raw, gl, &flag);
+      ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase);
     }
-    // (a pass that only fills the cache ends with the last layer's keys and values)
-    if (!ok || (p.kv_only && l == p.L - 1)) break;
-    grid_arrive(sy, phase++);
-    ok = attn_phase<MB, DH>(p, l, phase, lds_raw, &flag);
     if (!ok) break;
     grid_arrive(sy, phase++);
-    ok = resid_phase(STEP_O, l);
-    if (!ok) break;
-    grid_arrive(sy, phase++);
-    if (MB == 8 && p.step[STEP_GATE_UP].split_rows) {
-      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase, lds_raw, gl, &flag);
+    // split-K with row-split tiles at 128 rows, split-K with K-split tiles, or
+    // every block over the full K
+    const int step = ffn ? STEP_DOWN : STEP_O;
+    if (MB == 8 && p.step[step].split_rows) {
+      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_RESID>(p, step, l, phase);
+    } else if (p.step[step].split > 1) {
+      ok = split_phase<MB, EPI_RESID>(p, step, l, phase);
     } else {
-      ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase, lds_raw, gl, &flag);
+      ok = gemm_phase<MB, EPI_RESID>(p, step, l, phase);
     }
-    if (!ok) break;
-    grid_arrive(sy, phase++);
-    ok = resid_phase(STEP_DOWN, l);
     if (!ok) break;
     grid_arrive(sy, phase++);
   }
-  if (ok && !p.kv_only) ok = final_norm_phase<MB>(p, phase, gl, &flag);
+  if (ok && !p.kv_only) ok = final_norm_phase<MB>(p, phase);
   if (ok && !p.kv_only) {  // LM head + argmax + accept walk
     grid_arrive(sy, phase++);
-    if (gemm_phase<MB, EPI_LOGITS>(p, STEP_LM, 0, phase, lds_raw, gl, &flag)) trace_mark(sy, phase, 2);
+    if (gemm_phase<MB, EPI_LOGITS>(p, STEP_LM, 0, phase)) trace_mark(sy, phase, 2);
   }
   // Leave the pass: the last workgroup out resets the barrier and split-K
   // group counters.
-  if (arrive_last(p.exit_cnt, p.G, &flag)) {
+  if (arrive_last(p.exit_cnt, p.G, wait_flag())) {
     if (threadIdx.x < kBarSlots) st_coherent(p.bar + threadIdx.x * kBarStride, 0);
     for (int step = 0; step < STEP_LM; ++step)
       if (p.step[step].split > 1)
@@ -2569,24 +2590,15 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
 
 template <int MB, int DH, bool WIDE>
 hipError_t launch_pass_mb(KParams& p, const TreeArgs& tree, hipStream_t st) {
-  static bool attr_set = false;  // per process; the attribute is per function
-  const void* fn = (const void*)pass_kernel<MB, DH, WIDE>;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds_bytes<DH>());
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
   void* args[] = {(void*)&p, (void*)&tree};
-  return hipLaunchCooperativeKernel(fn, dim3(p.G), dim3(kThreads), args, (unsigned)dyn_lds_bytes<DH>(), st);
+  return hipLaunchCooperativeKernel((const void*)pass_kernel<MB, DH, WIDE>, dim3(p.G), dim3(kThreads), args, 0u, st);
 }
 
 template <int MB, int DH, bool WIDE>
 int occupancy_mb() {
-  const void* fn = (const void*)pass_kernel<MB, DH, WIDE>;
-  if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds_bytes<DH>()) != hipSuccess)
-    return 0;
   int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, kThreads, dyn_lds_bytes<DH>()) != hipSuccess)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)pass_kernel<MB, DH, WIDE>, kThreads, 0) !=
+      hipSuccess)
     return 0;
   return blocks;
 }
@@ -2644,11 +2656,6 @@ int pass_occupancy(int mb16, int dh, bool wide) {
 bool split_rows_fits(int cw, int oc, bool epi) {
   return cw <= kSplitTile && (cw - oc) * 8 * 1024 + (epi ? wl_off(oc, 8, 1) : epi_off(oc, 8, 1)) <= kGemmLdsBytes &&
          epi_off(cw, 8, 1) <= kGemmLdsBytes;
-}
-
-size_t pass_lds_bytes(int mb16, int dh) {
-  (void)mb16;
-  return dh == 128 ? dyn_lds_bytes<128>() : dyn_lds_bytes<64>();
 }
 
 }  // namespace llmcad
