@@ -145,7 +145,8 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   const PackedLayout P(s);
   const int G = pass_grid();
   const WorkspaceLayout W(s, a.n, G);
-  const int MB = W.Mp / 16;
+  // the instance for the 16-row blocks that hold nodes (kernels.h)
+  const int MB = pass_blocks(a.n);
   const bool wide = gate_up_wide(s, W.Mp, G);
   const int occ = pass_occupancy(MB, s.Dh, wide);
   if (device_info().cus <= 0 || occ * device_info().cus < G) {

@@ -119,7 +119,12 @@ struct PassParams {
   long long* trace;  // diagnostics: [G][4 + 5L][8] phase timestamps, or null
 };
 
-// mb16: 16-row blocks of the pass (Mp / 16: 1, 2, 4 or 8).
+// mb16: 16-row blocks of the pass that the kernel instance computes: 1, 2, 3,
+// 4, 6 or 8 (Mp / 16, or less where whole blocks of the layout are empty).
+inline int pass_blocks(int n) {
+  const int mb = cdiv(n, 16);
+  return mb <= 4 ? mb : mb <= 6 ? 6 : 8;
+}
 hipError_t launch_pass(int mb16, const PassParams& p, const TreeArgs& tree, hipStream_t st);
 // Whether a group of cw blocks, of which a workgroup finishes up to oc, fits one
 // row-split tile of a 128-row pass (epi: the step has epilogue inputs).

@@ -57,6 +57,14 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 
+// Kernel instances by MB, the 16-row blocks of the pass that hold nodes: 1, 2,
+// 3, 4, 6 (5 or 6) and 8.  Buffers are laid out for 1, 2, 4 or 8 (the pass's Mp
+// rows); the instances of 3 and 6 neither load nor multiply the empty rest of
+// theirs.  (41 nodes with 3 blocks instead of 4: 7B after 2048 positions 4337 ->
+// 4039 us per pass, 13B 6794 -> 6264; 77 nodes with 6 instead of 8, 4-bit 7B:
+// 5048 -> 4291.)
+__host__ __device__ constexpr int layout_mb(int MB) { return MB <= 2 ? MB : MB <= 4 ? 4 : 8; }
+
 // Tuning constants of the GEMM phases (the defaults were measured best on the
 // LLaMA-7B workload; -D overrides them for sweeps): the VGPRs (in units of 4)
 // a tile's register pipeline may hold, its depth for one-block and for wider
@@ -412,6 +420,11 @@ __device__ __forceinline__ void epilogue_inputs(KParams& p, const TileIn& io, in
       dma16(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1), epi + (size_t)(cw * MB + c) * 1024);
 }
 
+// Widest K-split tile (a gate/up step marked wide: 9 at 16 and 32 rows).
+__host__ __device__ constexpr int tile_max_blocks(int MB) {
+  return MB <= 3 ? 8 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
+}
+
 // Register stages per wave: at most ~160 VGPRs of them, and few -- 8 for
 // one-block tiles, 4 for wider ones.  The bytes in flight across a barrier
 // come mostly from the stages copied to LDS before it; a deeper register
@@ -459,7 +472,8 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   // this wave's k-steps: k0 + wave + 4 i
   const bf16x8* wt = io.w + ((size_t)nb0 * io.ks + k0 + wave) * 64 + lane;
   const size_t cstride = (size_t)io.ks * 64;
-  const bf16x8* at = io.a + (size_t)(k0 + wave) * MB * 64 + lane;
+  constexpr int LMB = layout_mb(MB);
+  const bf16x8* at = io.a + (size_t)(k0 + wave) * LMB * 64 + lane;
   // Loads past the wave's last k-step read a line of zeros instead (the
   // load is still issued, so that the compiler's count of loads in flight
   // stays exact and every wait in the loop is for one stage only).  For the
@@ -484,7 +498,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   auto load_a = [&](int slot, int i) {
     const bool live = i < ns;
 #pragma unroll
-    for (int rb = 0; rb < MB; ++rb) ba[slot][rb] = ldg(opaque(live ? at + ((size_t)kWaves * i * MB + rb) * 64 : zero));
+    for (int rb = 0; rb < MB; ++rb) ba[slot][rb] = ldg(opaque(live ? at + ((size_t)kWaves * i * LMB + rb) * 64 : zero));
   };
 
   // Before the barrier, waves 1-3 start the weight stream: each its own
@@ -682,6 +696,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
 // loop of 42 us with write, barrier, read and product in a row).  No partial sums cross waves: each
 // wave writes its rows' tiles to the one partial-tile slot.
 // k-steps [k0, k0 + kn) of the step's (all of them, or a split-K slice).
+__host__ __device__ constexpr bool has_row_tiles(int MB) { return MB >= 3; }
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KParams& pin, int step, int layer,
                                                                             int nb0, int wait_phase, int k0, int kn,
@@ -697,13 +712,14 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
   epi_in = wave_uniform(epi_in);
   const TileIn io = tile_in(p, step, layer);
   const int wave = wave_index(), lane = threadIdx.x & 63;
-  constexpr int RB = MB / kWaves;              // row blocks per wave
+  constexpr int RB = (MB + kWaves - 1) / kWaves;  // row blocks per wave (MB 3 and 6: the last wave has none)
+  constexpr int LMB = layout_mb(MB);
   constexpr int NW = (C + kWaves - 1) / kWaves;  // weight fragments per wave per k-step
-  static_assert(RB >= 1 && RB * kWaves == MB, "row-split tiles need 4 or 8 row blocks");
+  static_assert(has_row_tiles(MB), "row-split tiles are for passes of more than 32 rows");
   constexpr int DR = LLMCAD_STAGE_REGS / (NW + RB);
   constexpr int D = DR < 4 ? 2 : DR > LLMCAD_ROW_DEPTH ? LLMCAD_ROW_DEPTH : DR / 2 * 2;
   const size_t cstride = (size_t)io.ks * 64;
-  const bf16x8* at = io.a + ((size_t)k0 * MB + wave * RB) * 64 + lane;
+  const bf16x8* at = io.a + ((size_t)k0 * LMB + wave * RB) * 64 + lane;
   const bf16x8* wt = io.w + ((size_t)(nb0 + wave) * io.ks + k0) * 64 + lane;
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
   bf16x8 bw[D][NW];
@@ -717,9 +733,9 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
     }
   };
   auto load_a = [&](int slot, int i) {
-    const bool live = i < ks;
+    const bool live = i < ks && wave * RB < MB;
 #pragma unroll
-    for (int r = 0; r < RB; ++r) ba[slot][r] = ldg(opaque(live ? at + ((size_t)i * MB + r) * 64 : zero));
+    for (int r = 0; r < RB; ++r) ba[slot][r] = ldg(opaque(live ? at + ((size_t)i * LMB + r) * 64 : zero));
   };
   // two LDS buffers of C KiB: k-step i's fragments in buffer i % 2, block c at c KiB
   auto share_w = [&](int slot, int i) {
@@ -794,11 +810,13 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
   for (int u = 0; u < D; ++u)
     if (i + u < ks) kstep(i + u, u, false);
   // this wave's rows -> the one slot: unit (block c, row block rb) at (c MB + rb) KiB
+  if (wave * RB < MB) {
 #pragma unroll
-  for (int c = 0; c < C; ++c)
+    for (int c = 0; c < C; ++c)
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
-      lds_st<f32x4>(lds + tw_off() + ((size_t)(c * MB + wave * RB + r) * 64 + lane) * 16, acc[r][c]);
+      for (int r = 0; r < RB; ++r)
+        lds_st<f32x4>(lds + tw_off() + ((size_t)(c * MB + wave * RB + r) * 64 + lane) * 16, acc[r][c]);
+  }
   if (epi_in) epilogue_inputs<MB>(p, io, step, nb0, C, lds + epi_off(C, MB, 1), 0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
@@ -836,7 +854,7 @@ __device__ __forceinline__ bf16x8 q4_operand(uint32_t w, uint32_t mask, uint32_t
 // than four row blocks' accumulators; every activation is still read by one
 // wave only, and each code is dequantised 4 / KW times).  The tile leaves KW
 // partial-tile slots.
-__host__ __device__ constexpr int q4_kways(int MB) { return MB >= 8 ? 2 : 4; }
+__host__ __device__ constexpr int q4_kways(int MB) { return MB > 4 ? 2 : 4; }
 
 // Widest 4-bit tile: the partial tiles and the epilogue inputs (which the
 // gate/up step does not have) fit the LDS region.  (Gate/up tiles of 8 blocks
@@ -846,7 +864,7 @@ __host__ __device__ constexpr int q4_kways(int MB) { return MB >= 8 ? 2 : 4; }
 template <int MB, int EPI>
 constexpr int q4_tile_blocks() {
   if (MB <= 2) return 8;
-  return MB == 4 ? 6 : EPI == EPI_SWIGLU ? 6 : 5;
+  return MB <= 6 ? 6 : EPI == EPI_SWIGLU ? 6 : 5;
 }
 
 // 4-bit tile: blocks [nb0, nb0 + C) of a layer step over its scale groups
@@ -883,7 +901,8 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   epi_in = wave_uniform(epi_in);
   const TileIn io = tile_in(p, step, layer);
   const int wave = wave_index(), lane = threadIdx.x & 63;
-  constexpr int KW = q4_kways(MB), RW = kWaves / KW, RB = MB / RW;
+  constexpr int KW = q4_kways(MB), RW = kWaves / KW, RB = MB / RW, LMB = layout_mb(MB);
+  static_assert(RB * RW == MB, "the waves split the rows evenly");
   const int kw = wave % KW, rw = wave / KW;
   const int gs = io.ks;  // scale groups of the matrix
   const int ns = wave_uniform(kw < kn ? (kn - kw + KW - 1) / KW : 0);  // this wave's: k0 + kw + KW i
@@ -892,7 +911,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
   const size_t cstride = (size_t)gs * 64;
   const uint16_t* st = io.sc + ((size_t)nb0 * gs + k0 + kw) * kNB + 4 * (lane >> 4);  // (this lane's four columns)
   const size_t sstride = (size_t)gs * kNB;
-  const bf16x8* at = io.a + ((size_t)(k0 + kw) * 4 * MB + rw * RB) * 64 + lane;
+  const bf16x8* at = io.a + ((size_t)(k0 + kw) * 4 * LMB + rw * RB) * 64 + lane;
   const u32x4* zero_w = (const u32x4*)p.zero + lane;
   const uint16_t* zero_s = (const uint16_t*)p.zero;
   const bf16x8* zero = (const bf16x8*)p.zero + lane;
@@ -939,7 +958,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
-        ba[slot][t][rb] = ldg(opaque(live ? at + ((size_t)KW * 4 * i * MB + t * MB + rb) * 64 : zero));
+        ba[slot][t][rb] = ldg(opaque(live ? at + ((size_t)KW * 4 * i * LMB + t * LMB + rb) * 64 : zero));
   };
   // Before the barrier, by waves 1-3 (wave 0 polls it with no load in flight):
   // the epilogue inputs (residual rows or rotary table, and the next norm's
@@ -1184,7 +1203,7 @@ __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io) {
   if (MB <= 2 && p.ssq_regs)
     chunk_scales<MB>(p);
   else
-    row_rstd<MB>(p, io.ssq);
+    row_rstd<layout_mb(MB)>(p, io.ssq);
 }
 
 // Epilogue of one accumulator tile ("unit": block c of the tile x row block
@@ -1261,7 +1280,7 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
       float* dst = io.x_out + (size_t)r * p.d + col;
       st_coherent2(dst, xn[0], xn[1]);
       st_coherent2(dst + 2, xn[2], xn[3]);
-      st_coherent_bf4(io.xg_out + frag_off(r, col, MB), xg);
+      st_coherent_bf4(io.xg_out + frag_off(r, col, layout_mb(MB)), xg);
       if (g == 0) st_coherent(io.ssq_out + (size_t)nb * p.Mp + r, sq);
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -1272,7 +1291,7 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
       pair_xor32(v[i], gate, up);
       hv[i] = gate / (1.0f + expf(-gate)) * up;
     }
-    if (r < p.n && g < 2) st_coherent_bf4(io.h + frag_off(r, 8 * nb + 4 * g, MB), hv);
+    if (r < p.n && g < 2) st_coherent_bf4(io.h + frag_off(r, 8 * nb + 4 * g, layout_mb(MB)), hv);
   } else {  // EPI_LOGITS
     // (with candidate summaries the end of the pass reads the stored rows
     // back: device-coherent stores)
@@ -1683,7 +1702,7 @@ __device__ __forceinline__ bool split_phase(KParams& pin, int step, int layer,
   phase = wave_uniform(phase);
   const Sync sy = make_sync(p);
   const StepPlan& sp = p.step[step];
-  constexpr int CM = MB <= 2 ? 8 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
+  constexpr int CM = tile_max_blocks(MB);
   const int S = wave_uniform(sp.split), G = p.G, NG = G / S;
   const int nbk = sp.nblocks, ks = sp.ksteps;
   const int vw = virtual_wg(G);
@@ -1881,7 +1900,7 @@ __device__ __forceinline__ bool gemm_phase(KParams& pin, int step, int layer,
   const StepPlan& sp = p.step[step];
   // (CM2: 8, or 9 for a step marked wide; the LM head keeps 8, its per-block
   // argmax slots)
-  constexpr int CM = MB <= 2 ? CM2 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
+  constexpr int CM = MB <= 2 ? CM2 : tile_max_blocks(MB);
   static_assert(wl_off(CM, MB, tile_slots(CM, MB)) <= kGemmLdsBytes,
                 "a tile's partial sums and epilogue inputs fit the LDS");
   static_assert(EPI != EPI_LOGITS || CM2 <= 8, "the LM head's per-block argmax slots");
@@ -1893,12 +1912,12 @@ __device__ __forceinline__ bool gemm_phase(KParams& pin, int step, int layer,
   // once instead of once per tile (where one K-split tile holds them all,
   // that tile is faster: no barrier per k-step).
   constexpr int CMR = 8;
-  static_assert(MB < 4 || wl_off(CMR, MB, 1) <= kGemmLdsBytes, "a row-split tile fits the LDS");
+  static_assert(!has_row_tiles(MB) || wl_off(CMR, MB, 1) <= kGemmLdsBytes, "a row-split tile fits the LDS");
   const bool q4 = wave_uniform(sp.q4) != 0;
   const int nbk = sp.nblocks, G = p.G;
   const int vw = virtual_wg(G);
   const int lo = run_start(p, vw, nbk), hi = run_start(p, vw + 1, nbk);
-  const bool rows = MB >= 4 && !q4 && wave_uniform(p.row_tiles) != 0 && hi - lo > CM;
+  const bool rows = has_row_tiles(MB) && !q4 && wave_uniform(p.row_tiles) != 0 && hi - lo > CM;
   const int cm = q4 ? CMQ : rows ? CMR : CM;
   if constexpr (EPI == EPI_LOGITS) {
     GemmLds& gl = gemm_lds();
@@ -1919,7 +1938,7 @@ __device__ __forceinline__ bool gemm_phase(KParams& pin, int step, int layer,
     const int cw = hi - b0 < cm ? hi - b0 : cm;
     const bool first = b0 == lo;
     bool ok;
-    if constexpr (MB >= 4) {
+    if constexpr (has_row_tiles(MB)) {
       ok = q4     ? tile_dispatch_q4<MB, CMQ>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1)
            : rows ? tile_dispatch_rows<MB, CMR>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1)
                   : tile_dispatch<MB, CM>(cw, p, step, layer, b0, first ? phase : -1, 0, sp.ksteps, 1);
@@ -2515,7 +2534,8 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
   __shared__ int par_s[128];
   // The parameter block is the first kernel argument: read it in place.
   KParams& p = *(KParams*)__builtin_amdgcn_kernarg_segment_ptr();
-  if (p.magic != kPassMagic || p.G != p_arg.G || p.n != p_arg.n || p.Mp != 16 * MB) {
+  constexpr int LMB = layout_mb(MB);
+  if (p.magic != kPassMagic || p.G != p_arg.G || p.n != p_arg.n || p.Mp != 16 * LMB || p.n > 16 * MB) {
     if (threadIdx.x == 0 && blockIdx.x == 0) stg(p_arg.status, 3);
     return;  // (uniform over the grid: no workgroup reaches a barrier)
   }
@@ -2523,7 +2543,7 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
   int phase = 0;
   bool ok = true;
 
-  embed_phase<MB>(p, tree, par_s);
+  embed_phase<LMB>(p, tree, par_s);
   grid_arrive(sy, phase);
   ++phase;
   // The QKV phases load the rotary table before they wait at their barrier
@@ -2543,17 +2563,17 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
     const int l = s >> 1;
     const bool ffn = (s & 1) != 0;
     if (!ffn) {
-      if (MB == 8 && p.step[STEP_QKV].split_rows) {
-        if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase);
+      if (MB > 4 && p.step[STEP_QKV].split_rows) {
+        if constexpr (MB > 4) ok = split_rows_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase);
       } else {
         ok = gemm_phase<MB, EPI_QKV>(p, STEP_QKV, l, phase);
       }
       // (a pass that only fills the cache ends with the last layer's keys and values)
       if (!ok || (p.kv_only && l == p.L - 1)) break;
       grid_arrive(sy, phase++);
-      ok = attn_phase<MB, DH>(p, l, phase);
-    } else if (MB == 8 && p.step[STEP_GATE_UP].split_rows) {
-      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase);
+      ok = attn_phase<LMB, DH>(p, l, phase);
+    } else if (MB > 4 && p.step[STEP_GATE_UP].split_rows) {
+      if constexpr (MB > 4) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase);
     } else {
       ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase);
     }
@@ -2562,8 +2582,8 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
     // split-K with row-split tiles at 128 rows, split-K with K-split tiles, or
     // every block over the full K
     const int step = ffn ? STEP_DOWN : STEP_O;
-    if (MB == 8 && p.step[step].split_rows) {
-      if constexpr (MB == 8) ok = split_rows_phase<MB, EPI_RESID>(p, step, l, phase);
+    if (MB > 4 && p.step[step].split_rows) {
+      if constexpr (MB > 4) ok = split_rows_phase<MB, EPI_RESID>(p, step, l, phase);
     } else if (p.step[step].split > 1) {
       ok = split_phase<MB, EPI_RESID>(p, step, l, phase);
     } else {
@@ -2572,7 +2592,7 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
     if (!ok) break;
     grid_arrive(sy, phase++);
   }
-  if (ok && !p.kv_only) ok = final_norm_phase<MB>(p, phase);
+  if (ok && !p.kv_only) ok = final_norm_phase<LMB>(p, phase);
   if (ok && !p.kv_only) {  // LM head + argmax + accept walk
     grid_arrive(sy, phase++);
     if (gemm_phase<MB, EPI_LOGITS>(p, STEP_LM, 0, phase)) trace_mark(sy, phase, 2);
@@ -2615,7 +2635,9 @@ hipError_t launch_pass(int mb16, KParams& p, const TreeArgs& tree, hipStream_t s
     switch (mb16) {
       LLMCAD_PASS_CASE(1, false)
       LLMCAD_PASS_CASE(2, false)
+      LLMCAD_PASS_CASE(3, false)
       LLMCAD_PASS_CASE(4, false)
+      LLMCAD_PASS_CASE(6, false)
       LLMCAD_PASS_CASE(8, false)
       default:
         return hipErrorInvalidValue;
@@ -2638,7 +2660,9 @@ int pass_occupancy(int mb16, int dh, bool wide) {
     switch (mb16) {
       LLMCAD_OCC_CASE(1, false)
       LLMCAD_OCC_CASE(2, false)
+      LLMCAD_OCC_CASE(3, false)
       LLMCAD_OCC_CASE(4, false)
+      LLMCAD_OCC_CASE(6, false)
       LLMCAD_OCC_CASE(8, false)
       default:
         return 0;

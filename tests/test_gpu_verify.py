@@ -106,6 +106,16 @@ def test_verify_matches_oracle(model, tree):
     _check_all(model, parent, tok, f"{model.shape.name}/{tree}")
 
 
+@pytest.mark.parametrize("n", [16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 113])
+def test_row_block_edges(model, n):
+    # Kernel instances by the 16-row blocks that hold nodes (1, 2, 3, 4, 6 and
+    # 8): the node counts on either side of every switch between two of them,
+    # and of every block.
+    parent = workloads.random_tree(n, 7, n)
+    tok = workloads.draw_tokens(n, model.shape.vocab, seed=37, stream=n)
+    _check_all(model, parent, tok, f"{model.shape.name}/n{n}")
+
+
 def test_launch_shape_variants(model, monkeypatch):
     # One and four key splits in the attention, and smaller grids (each
     # workgroup then takes longer runs of column blocks, cut into several
