@@ -128,7 +128,7 @@ inline int pass_blocks(int n) {
 hipError_t launch_pass(int mb16, const PassParams& p, const TreeArgs& tree, hipStream_t st);
 // Whether a group of cw blocks, of which a workgroup finishes up to oc, fits one
 // row-split tile of a 128-row pass (epi: the step has epilogue inputs).
-bool split_rows_fits(int cw, int oc, bool epi);
+bool split_rows_fits(int cw, int oc, bool epi, bool q4);
 int pass_occupancy(int mb16, int dh, bool wide);  // resident workgroups per CU (0 if unavailable)
 
 

@@ -1785,7 +1785,10 @@ __device__ __forceinline__ bool split_phase(KParams& pin, int step, int layer,
 // activations and weights, 953 with S = 2 and the exchange; O 1152, 430 with
 // S = 4; down 3168, 1760 with S = 2, 1100 with S = 4 (loops of 23.6 -> 18.9 us,
 // and 25.5 -> 20.1 us for down in fours instead of pairs).
-constexpr int kSplitTile = 12;
+// 4-bit steps run the same way with their own tiles of up to kSplitTileQ4
+// blocks: their codes are a quarter of the weights, so the activations weigh
+// more (77 nodes, O and down in pairs: 4291 -> 4026 us per pass).
+constexpr int kSplitTile = 12, kSplitTileQ4 = 6;
 
 // Adds the other slices' partial tiles (slice t's from src + t stride floats,
 // unit u at + 256 u) to this workgroup's own, slice sl's, in LDS, in slice
@@ -1842,7 +1845,17 @@ __device__ __forceinline__ bool split_rows_phase(KParams& pin, int step, int lay
   const int wave = wave_index(), lane = threadIdx.x & 63;
   constexpr int U = MB * 256;  // floats of one block's partial tiles
   int* cnt = p.grp_cnt + step * kSplitGroups + g;
-  if (!tile_dispatch_rows<MB, kSplitTile>(cw, p, step, layer, glo, phase, k0, k1 - k0, 0)) return false;
+  if (wave_uniform(sp.q4) != 0) {  // (4-bit: its own tiles, whose ways' partial tiles are added into the first slot)
+    if (!tile_dispatch_q4<MB, kSplitTileQ4>(cw, p, step, layer, glo, phase, k0, k1 - k0, 0)) return false;
+    static_assert(q4_kways(MB) == 2, "two slots");
+    for (int u = wave; u < cw * MB; u += kWaves) {
+      char* at = lds + tw_off() + ((size_t)u * 64 + lane) * 16;
+      lds_st<f32x4>(at, lds_ld<f32x4>(at) + lds_ld<f32x4>(at + (size_t)cw * MB * 1024));
+    }
+    __syncthreads();  // (the epilogue inputs go over the second slot)
+  } else if (!tile_dispatch_rows<MB, kSplitTile>(cw, p, step, layer, glo, phase, k0, k1 - k0, 0)) {
+    return false;
+  }
   trace_mark(sy, phase, 4);
   const int olo = wave_uniform(sl * cw / S), ohi = wave_uniform((sl + 1) * cw / S);  // the blocks it finishes
   float* mine = p.part + (size_t)vw * bstride * U;
@@ -2677,8 +2690,8 @@ int pass_occupancy(int mb16, int dh, bool wide) {
 #undef LLMCAD_OCC_CASE
 }
 
-bool split_rows_fits(int cw, int oc, bool epi) {
-  return cw <= kSplitTile && (cw - oc) * 8 * 1024 + (epi ? wl_off(oc, 8, 1) : epi_off(oc, 8, 1)) <= kGemmLdsBytes &&
+bool split_rows_fits(int cw, int oc, bool epi, bool q4) {
+  return cw <= (q4 ? kSplitTileQ4 : kSplitTile) && (cw - oc) * 8 * 1024 + (epi ? wl_off(oc, 8, 1) : epi_off(oc, 8, 1)) <= kGemmLdsBytes &&
          epi_off(cw, 8, 1) <= kGemmLdsBytes;
 }
 
