@@ -104,7 +104,6 @@ __device__ __forceinline__ void wave_argmax(float& v, int& idx) {
 constexpr int kDppQuadXor1 = 0xB1;       // quad_perm [1,0,3,2]: reads lane ^ 1
 constexpr int kDppQuadXor2 = 0x4E;       // quad_perm [2,3,0,1]: reads lane ^ 2
 constexpr int kDppRowShl1 = 0x101;       // row_shl:1: lane i of a row reads lane i + 1 (lane 15 gets 0)
-constexpr int kDppRowRor8 = 0x128;       // row_ror:8: reads lane (i + 8) mod 16, i.e. lane ^ 8
 constexpr int kDppRowMirror = 0x140;     // reads lane 15 - i of the row
 constexpr int kDppRowHalfMirror = 0x141; // reads lane 7 - i of the half row
 template <int CTRL>
@@ -125,8 +124,8 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 // Across rows: the values of lanes l and l ^ 16 (l ^ 32) of the wave, from
-// one gfx950 permlane swap of the value with itself (lane l gets both of its
-// pair, in an order that depends on l), on the vector ALU.
+// one gfx950 permlane swap of the value with itself, on the vector ALU: a is
+// the value of the pair's lower lane, b the upper one's, in both lanes.
 __device__ __forceinline__ void pair_xor16(float v, float& a, float& b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   a = __uint_as_float(r[0]);
