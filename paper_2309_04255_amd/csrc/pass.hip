@@ -253,10 +253,7 @@ struct GemmLds {
     float red_s[kMaxNodes][8];  // LM head: sum of exp(logit - red_v) per (row, block of the tile)
   };
   float red_v[kMaxNodes][8];    // LM head: argmax per (row, block of the tile)
-  union {
-    float part_ss2[512];        // the partial sums' sums by part
-    int red_i[kMaxNodes][8];
-  };
+  int red_i[kMaxNodes][8];
   float best_v[kMaxNodes];      // LM head: argmax per row over this workgroup's blocks
   int best_i[kMaxNodes];
   int reach[kMaxNodes];         // accept walk: reachability of each node,
@@ -420,6 +417,41 @@ __device__ __forceinline__ void epilogue_inputs(KParams& p, const TileIn& io, in
       dma16(io.g_next + kNB * (nb0 + c) + 8 * (lane & 1), epi + (size_t)(cw * MB + c) * 1024);
 }
 
+// RMSNorm scale of a row, 1 / sqrt(mean of squares + eps), 0 for rows >= n,
+// from its chunk sums in GemmLds::part_ss ([64 / MB][16 MB]), added in chunk
+// order.  (The additions are a chain of 64 / MB.  A tree over the workgroup is
+// shorter but rounds otherwise, and where a model's two best tokens are closer
+// than bf16 resolves the greedy tokens follow the rounding: a 30B pass over 8
+// nodes then takes another path.)
+template <int MB>
+__device__ __forceinline__ float row_scale(KParams& p, int row) {
+  GemmLds& gl = gemm_lds();
+  constexpr int ROWS = 16 * MB, CHK = 4 * kThreads / ROWS;
+  float t = 0.0f;
+#pragma unroll
+  for (int c = 0; c < CHK; ++c) t += gl.part_ss[c * ROWS + row];
+  return row < p.n ? 1.0f / sqrtf(t * p.inv_d + p.eps) : 0.0f;
+}
+
+// The chunk sums from the sums of squares a tile holds in registers (thread t:
+// rows 4 q .. 4 q + 3, q = t % (4 MB), of chunk t / (4 MB)).
+template <int MB, int N>
+__device__ __forceinline__ void chunk_sums(const f32x4 (&sr)[N]) {
+  constexpr int QUADS = 4 * MB;
+  const int q = threadIdx.x % QUADS, ch = threadIdx.x / QUADS;
+  f32x4 t = sr[0];
+#pragma unroll
+  for (int k = 1; k < N; ++k) t += sr[k];
+  *(f32x4*)&gemm_lds().part_ss[ch * 16 * MB + 4 * q] = t;
+}
+
+// Where a pass of 16 or 32 rows adds them up: at 16 rows before the main loop,
+// by the last wave, its chain of 64 behind the other waves' loads (1B draft
+// step 1157 us per pass, 1173 with the chain in the epilogue); at 32 rows in the
+// epilogue (7B, 31 nodes: 3227 us per pass, 3267 before the loop, where every
+// wave's sums come between its first loads and its first product).
+__host__ __device__ constexpr bool scales_before_loop(int MB) { return MB == 1; }
+
 // Widest K-split tile (a gate/up step marked wide: 9 at 16 and 32 rows).
 __host__ __device__ constexpr int tile_max_blocks(int MB) {
   return MB <= 3 ? 8 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
@@ -449,7 +481,6 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
                                                                        int nb0, int wait_phase, int k0, int kn,
                                                                        int epi_in) {
   char* const lds = lds_region();
-  GemmLds& gl = gemm_lds();
   KParams& p = uniform_params(pin);
   step = wave_uniform(step);
   layer = wave_uniform(layer);
@@ -563,10 +594,16 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   // count them exactly), and wave 0's LDS stages, copied by wave 1, are
   // visible to it.  Then wave 0's register stages.
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (scales_before_loop(MB)) {
+    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
+  }
   lds_barrier();
   if (wave == 0) {
 #pragma unroll
     for (int u = 0; u < D; ++u) load_w(u, P + u, true);
+  }
+  if constexpr (scales_before_loop(MB)) {
+    if (wave == kWaves - 1 && io.norm && p.ssq_regs && lane < 16 * MB) gemm_lds().rstd[lane] = row_scale<MB>(p, lane);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0 && p.trace != nullptr && threadIdx.x == 0)
@@ -623,15 +660,8 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (SSQR) {
-    if (io.norm && p.ssq_regs) {
-      constexpr int QUADS = 4 * MB;
-      const int q = threadIdx.x % QUADS, ch = threadIdx.x / QUADS;
-      f32x4 t = sr[0];
-#pragma unroll
-      for (int k = 1; k < SSQN; ++k) t += sr[k];
-      *(f32x4*)&gl.part_ss[ch * 16 * MB + 4 * q] = t;
-    }
+  if constexpr (SSQR && !scales_before_loop(MB)) {
+    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
   }
   // This wave's partial tile -> LDS; the epilogue adds the four in wave
   // order.  With two slots, waves 2 and 3 hand theirs to waves 0 and 1
@@ -888,7 +918,6 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
                                                                           int nb0, int wait_phase, int k0, int kn,
                                                                           int epi_in) {
   char* const lds = lds_region();
-  GemmLds& gl = gemm_lds();
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   KParams& p = uniform_params(pin);
@@ -1004,10 +1033,16 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 #pragma unroll
   for (int u = 0; u < D; ++u) load_a(u, u);
   __builtin_amdgcn_s_waitcnt(0);
+  if constexpr (scales_before_loop(MB)) {
+    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
+  }
   lds_barrier();
   if (wave == 0) {
 #pragma unroll
     for (int u = 0; u < D; ++u) load_w(u, P + u);
+  }
+  if constexpr (scales_before_loop(MB)) {
+    if (wave == kWaves - 1 && io.norm && p.ssq_regs && lane < 16 * MB) gemm_lds().rstd[lane] = row_scale<MB>(p, lane);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0 && p.trace != nullptr && threadIdx.x == 0)
@@ -1093,15 +1128,8 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (SSQR) {
-    if (io.norm && p.ssq_regs) {
-      constexpr int QUADS = 4 * MB;
-      const int q = threadIdx.x % QUADS, ch = threadIdx.x / QUADS;
-      f32x4 t = sr[0];
-#pragma unroll
-      for (int k = 1; k < SSQN; ++k) t += sr[k];
-      *(f32x4*)&gl.part_ss[ch * 16 * MB + 4 * q] = t;
-    }
+  if constexpr (SSQR && !scales_before_loop(MB)) {
+    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
   }
   lds_barrier();  // (the slots' room may hold codes another wave still reads)
 #pragma unroll
@@ -1140,38 +1168,8 @@ __device__ __forceinline__ float rope_inv_freq(int j, int Dh, float log2_theta) 
   return exp2f(-(2.0f * (float)j / (float)Dh) * log2_theta);
 }
 
-// RMSNorm scales of rows [0, Mp) into gl.rstd, 1 / sqrt(mean of squares +
-// eps), 0 for rows >= n, from the chunk sums in gl.part_ss ([64 / MB][16 MB]):
-// thread t adds the four of row t % (16 MB), part t / (16 MB); the parts meet
-// across the wave, then (gl.part_ss2) across the waves, in a fixed order.  (One
-// thread per row adding up to 64 chunks in turn: +0.2 us per epilogue.)
-template <int MB>
-__device__ __forceinline__ void chunk_scales(KParams& p) {
-  GemmLds& gl = gemm_lds();
-  constexpr int ROWS = 16 * MB, NP = ROWS < 64 ? kWaves : kThreads / ROWS;
-  const int row = threadIdx.x % ROWS, part = threadIdx.x / ROWS;
-  float t = 0.0f;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) t += gl.part_ss[(4 * part + e) * ROWS + row];
-  if constexpr (MB == 1) {
-    t = col4_sum(t);
-  } else if constexpr (MB == 2) {
-    float a, b;
-    pair_xor32(t, a, b);
-    t = a + b;
-  }
-  if (ROWS >= 64 || (threadIdx.x & 63) < ROWS) gl.part_ss2[(ROWS < 64 ? wave_index() : part) * ROWS + row] = t;
-  __syncthreads();
-  if (threadIdx.x < ROWS) {
-    float u = 0.0f;
-#pragma unroll
-    for (int k = 0; k < NP; ++k) u += gl.part_ss2[k * ROWS + threadIdx.x];
-    gl.rstd[threadIdx.x] = threadIdx.x < p.n ? 1.0f / sqrtf(u * p.inv_d + p.eps) : 0.0f;
-  }
-  __syncthreads();
-}
-
-// The same from a version's sums of squares ssq [d/16][Mp].
+// The scales of rows [0, Mp) into gl.rstd from a version's sums of squares
+// ssq [d/16][Mp].
 template <int MB>
 __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq) {
   GemmLds& gl = gemm_lds();
@@ -1193,17 +1191,20 @@ __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq) {
   }
   *(f32x4*)&gl.part_ss[ch * ROWS + 4 * q] = ss;
   __syncthreads();
-  chunk_scales<MB>(p);
+  if (threadIdx.x < ROWS) gl.rstd[threadIdx.x] = row_scale<MB>(p, threadIdx.x);
+  __syncthreads();
 }
 
-// A norm step's row scales; when its tile held the sums of squares in
-// registers the chunk sums are in part_ss already.
+// A norm step's row scales, into gl.rstd.  When its tile held the sums of squares
+// in registers they are there already, or their chunk sums are.
 template <int MB>
 __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io) {
-  if (MB <= 2 && p.ssq_regs)
-    chunk_scales<MB>(p);
-  else
+  if (MB > 2 || !p.ssq_regs) {
     row_rstd<layout_mb(MB)>(p, io.ssq);
+  } else if constexpr (!scales_before_loop(MB)) {
+    if (threadIdx.x < 16 * MB) gemm_lds().rstd[threadIdx.x] = row_scale<MB>(p, threadIdx.x);
+    __syncthreads();
+  }
 }
 
 // Epilogue of one accumulator tile ("unit": block c of the tile x row block
@@ -1269,13 +1270,17 @@ __device__ __forceinline__ void epilogue_unit(KParams& p, const StepIo& io, cons
     const f32x4 xin = lds_ld<f32x4>(epi + (size_t)unit * 1024 + (size_t)(li * 16 + 4 * g) * 4);
     const bf16x4 gn = lds_ld<bf16x4>(epi + (size_t)(cw * MB + c) * 1024 + 8 * g);
     f32x4 xn = xin + v, xg;
-    float sq = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      xg[i] = xn[i] * bf2f(gn[i]);
-      sq += xn[i] * xn[i];
-    }
-    sq = col4_sum(sq);  // sum of squares over the block's 16 columns
+    for (int i = 0; i < 4; ++i) xg[i] = xn[i] * bf2f(gn[i]);
+    // Sum of squares over the block's 16 columns.  A quarter's columns are taken
+    // in pairs, the second of each squared and rounded first: from its first
+    // column on in even quarters, from its last back in odd ones.  (The order
+    // of a butterfly over 16 lanes of one column each; it is part of what the
+    // pass returns, see row_scale.)
+    const bool odd = (g & 1) != 0;
+    const float y0 = odd ? xn[3] : xn[0], y1 = odd ? xn[2] : xn[1];
+    const float y2 = odd ? xn[1] : xn[2], y3 = odd ? xn[0] : xn[3];
+    const float sq = col4_sum(fmaf(y0, y0, y1 * y1) + fmaf(y2, y2, y3 * y3));
     if (r < p.n) {
       float* dst = io.x_out + (size_t)r * p.d + col;
       st_coherent2(dst, xn[0], xn[1]);

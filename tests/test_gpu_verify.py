@@ -9,6 +9,8 @@ Trees span one to eight 16-row blocks with ragged tails (n = 1 ... 128), and
 the prefix (100) is not a multiple of the 64-position attention chunk.
 """
 
+import hashlib
+import json
 import os
 import types
 
@@ -409,6 +411,37 @@ def test_logit_columns(vocab):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(out.view(n, vocab).cpu().numpy(), logits)
         assert torch.isnan(buf[:shift]).all() and torch.isnan(buf[shift + n * vocab:]).all()
+
+
+GOLDEN_BITS = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "pass_bits.json")
+
+
+def pass_digests(sess, PL, parent, tok):
+    """SHA-256 of a pass's logits (fp32) and of the keys and values it wrote (bf16)."""
+    n = len(parent)
+    sess.verify_tree(PL, tok, parent)
+    sess.results(n)
+    out = {"logits": sess.logits[:n], "k": sess.k_cache[:, :, PL:PL + n], "v": sess.v_rows[:, :, PL:PL + n]}
+    return {k: hashlib.sha256(t.contiguous().view(torch.uint8).cpu().numpy().tobytes()).hexdigest()
+            for k, t in out.items()}
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 32, 33, 64, 128])
+def test_pass_bits(model, n):
+    # The order of the fp32 sums -- a block's squares, a row's blocks, the waves'
+    # partial products -- is part of what a pass returns: with models whose two
+    # best tokens are closer than bf16 resolves, another order is another path.
+    # tests/golden/pass_bits.json holds digests of these passes (no split-K and
+    # one tile per workgroup at these shapes); a pass must return the same bits.
+    # (4-bit products have an order of their own, which is not pinned.)
+    if model.shape.weight_bits == 4:
+        pytest.skip("bf16 models")
+    sess = _long_prefix_session(model, 600)[0]
+    parent = workloads.random_tree(n, 7, n)
+    tok = workloads.draw_tokens(n, model.shape.vocab, seed=41, stream=n)
+    with open(GOLDEN_BITS) as f:
+        want = json.load(f)[f"{model.shape.name}/n{n}"]
+    assert pass_digests(sess, 600, parent, tok) == want
 
 
 def test_planted_tree(model):
