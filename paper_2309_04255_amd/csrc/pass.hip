@@ -79,7 +79,7 @@ __host__ __device__ constexpr int layout_mb(int MB) { return MB <= 2 ? MB : MB <
 #ifndef LLMCAD_DEPTH_WIDE
 #define LLMCAD_DEPTH_WIDE 4
 #endif
-#ifndef LLMCAD_ROW_DEPTH  // most stages of a row-split tile (7B, 128 rows, us per pass: 6317 with 2, 5753 with 4, 5502 with 6, 5415 with 8; 10 is 1% behind 8)
+#ifndef LLMCAD_ROW_DEPTH  // most stages of a row-split tile, at least 4 (7B, 128 rows, us per pass: 5753 with 4, 5502 with 6, 5415 with 8; 10 is 1% behind 8)
 #define LLMCAD_ROW_DEPTH 8
 #endif
 #ifndef LLMCAD_TILE_BLOCKS_MB8
@@ -747,7 +747,11 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_rows(KPa
   constexpr int NW = (C + kWaves - 1) / kWaves;  // weight fragments per wave per k-step
   static_assert(has_row_tiles(MB), "row-split tiles are for passes of more than 32 rows");
   constexpr int DR = LLMCAD_STAGE_REGS / (NW + RB);
-  constexpr int D = DR < 4 ? 2 : DR > LLMCAD_ROW_DEPTH ? LLMCAD_ROW_DEPTH : DR / 2 * 2;
+  // k-step i shares k-step i + 2's weights, from the stage that k-step i + 2 - D
+  // refilled: with two stages that would be its own, not refilled yet, and with
+  // an odd number stages and LDS buffers would fall out of step.
+  constexpr int D = (DR < LLMCAD_ROW_DEPTH ? DR : LLMCAD_ROW_DEPTH) / 2 * 2;
+  static_assert(D >= 4, "a row-split tile's pipeline shares weights two k-steps ahead of its refill");
   const size_t cstride = (size_t)io.ks * 64;
   const bf16x8* at = io.a + ((size_t)k0 * LMB + wave * RB) * 64 + lane;
   const bf16x8* wt = io.w + ((size_t)(nb0 + wave) * io.ks + k0) * 64 + lane;
