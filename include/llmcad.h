@@ -356,6 +356,15 @@ const char* llmcad_status_string(int status);
 int llmcad_workspace_region(const llmcad_config* cfg, int32_t max_n, int32_t which, size_t* offset,
                             size_t* bytes);
 
+/* Diagnostics: how a pass over n nodes would share its layer steps between
+ * groups of workgroups on the current device (without one, on 256 CUs).
+ * plan (host int32 [4][3], caller owned) receives for QKV, O, gate/up and down:
+ * the workgroups sharing each group of 16-column blocks, each over a part of
+ * the inputs (1: no sharing); 1 if they run row-split or 4-bit tiles, 0 if
+ * K-split tiles; and the blocks of the largest group.
+ * Errors: LLMCAD_EARG for a NULL plan or n not in [1, 128]. */
+int llmcad_split_plan(const llmcad_config* cfg, int32_t n, int32_t* plan);
+
 /* Kernel classes for llmcad_timing_enable.  A verification or prefill pass
  * is one persistent launch. */
 #define LLMCAD_KERNEL_PASS 0

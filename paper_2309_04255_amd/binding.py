@@ -39,6 +39,7 @@ SYMBOLS = (
     "llmcad_extend_tree_candidates",
     "llmcad_status_string",
     "llmcad_workspace_region",
+    "llmcad_split_plan",
     "llmcad_timing_enable",
     "llmcad_timing_read",
 )
@@ -128,6 +129,7 @@ def _load():
         "llmcad_status_string": (ctypes.c_char_p, [ctypes.c_int]),
         "llmcad_workspace_region": (ctypes.c_int, [CFG, I32, I32, ctypes.POINTER(SZ),
                                                    ctypes.POINTER(SZ)]),
+        "llmcad_split_plan": (ctypes.c_int, [CFG, I32, I32P]),
         "llmcad_timing_enable": (ctypes.c_int, [I32, I32]),
         "llmcad_timing_read": (ctypes.c_int, [I32, ctypes.POINTER(ctypes.c_double), I32P]),
     }
@@ -348,6 +350,15 @@ def workspace_region(cfg, n: int, which: int):
     _check(_lib.llmcad_workspace_region(ctypes.byref(cfg), int(n), int(which), ctypes.byref(off),
                                         ctypes.byref(size)), "llmcad_workspace_region")
     return off.value, size.value
+
+
+def split_plan(cfg, n: int):
+    """Diagnostics: per layer step, how a pass over n nodes shares it between workgroups
+    (see llmcad_split_plan): {step: (workgroups per group, row-split or 4-bit tiles?, blocks of the largest group)}."""
+    plan = (ctypes.c_int32 * 12)()
+    _check(_lib.llmcad_split_plan(ctypes.byref(cfg), int(n), plan), "llmcad_split_plan")
+    return {name: (plan[3 * j], bool(plan[3 * j + 1]), plan[3 * j + 2])
+            for j, name in enumerate(("qkv", "o", "gate_up", "down"))}
 
 
 def timing_enable(kernel_class: int, max_launches: int):

@@ -140,6 +140,74 @@ bool gate_up_wide(const Shape& s, int Mp, int G) {
   return Mp <= 32 && !s.q4 && cdiv(step_blocks(s, STEP_GATE_UP), G) > 8;
 }
 
+// What a pass's steps are, but for where their weights lie.
+void plan_steps(const Shape& s, StepPlan* step) {
+  for (int i = 0; i < kSteps; ++i) {
+    StepPlan& sp = step[i];
+    sp.nblocks = step_blocks(s, i);
+    sp.layer_rel = i == STEP_LM ? 0 : 1;
+    sp.q4 = s.q4 && i != STEP_LM ? 1 : 0;
+    // bf16: k-steps of 32 inputs; 4-bit: scale groups of 128 inputs
+    sp.ksteps = sp.q4 ? step_groups(s, i) : step_ksteps(s, i);
+    sp.split = 1;
+    sp.split_rows = 0;
+  }
+}
+
+// (diagnostics: LLMCAD_ROW_TILES=2 turns the row-split tiles off)
+bool row_tiles_on() { return env_int("LLMCAD_ROW_TILES", 1) != 2; }
+
+// Split-K: groups of S workgroups share a group of column blocks, each over
+// 1/S of the k-steps, so each reads 1/S of the activations per block of
+// weights; the partial tiles meet in memory and each workgroup finishes 1/S
+// of the group's blocks.
+//
+// At 128 rows a CU's loads bound every step (see split_rows_phase); the groups
+// run row-split tiles (us per pass, LLaMA shapes; 77 nodes are 6 row blocks,
+// 128 are 8):
+// - O and the down projection in fours: O alone 5072 against 5153 at 7B and 128
+//   nodes, 9527 / 9657 at 13B, 20739 / 21026 at 30B; at 77 nodes within 0.3% at
+//   1B, 7B and 30B, 7874 / 7985 at 13B.  Down in pairs 5391 against 5130 (7B,
+//   128), 5058 / 4804 (7B, 77), 7980 / 7769 (13B, 77).
+// - QKV in pairs where a workgroup's blocks do not fit one K-split tile (30B:
+//   20168 against 20739 at 128 nodes, 19036 / 19755 at 77).  Where they do the
+//   exchange costs more than it saves: 5104 against 5072 (7B, 128), 4792 / 4649
+//   (7B, 77), 7994 / 7874 (13B, 77), 1728 / 1714 (1B, 77); 13B at 128 nodes is
+//   the closest, 9503 / 9527.
+// - Not gate/up: its groups' partial tiles are the largest and its weights alone
+//   take two thirds of the time.
+// - 4-bit steps: O and down in pairs (7B, 77 nodes: O alone 3887 against 3933,
+//   down alone 3887 / 4151; down in fours 3890.  128 nodes: 4558 / 4554, 4558 /
+//   4717, 4592).
+// At 64 rows the down projection in pairs, with K-split tiles (3 row blocks: 3968
+// against 4027 at 7B after 2048 positions, 6276 / 6557 at 13B; 4 row blocks: 3811
+// / 3955 at 7B), and not O (within 0.3%).  At 32 rows neither (7B).
+// (LLMCAD_SPLIT_QKV / _O / _DOWN, diagnostics, ask for 1, 2 or 4.)
+void plan_split_k(const Shape& s, const WorkspaceLayout& W, int G, StepPlan* step) {
+  const int steps[3] = {STEP_QKV, STEP_O, STEP_DOWN};
+  const char* names[3] = {"LLMCAD_SPLIT_QKV", "LLMCAD_SPLIT_O", "LLMCAD_SPLIT_DOWN"};
+  const bool qkv = !s.q4 && cdiv(step[STEP_QKV].nblocks, G) > pass_tile_blocks(8);
+  const int rows_s[3] = {qkv ? 2 : 1, s.q4 ? 2 : 4, s.q4 ? 2 : 4};  // with row-split (or 4-bit) tiles
+  const int k_s[3] = {1, 1, W.Mp >= 64 ? 2 : 1};                    // with K-split tiles
+  for (int j = 0; j < 3; ++j) {
+    StepPlan& sp = step[steps[j]];
+    // groups of S workgroups with at least a block each, whose partial tiles fit the region
+    auto groups = [&](int S) {
+      return (S == 2 || S == kMaxSplitK) && G % S == 0 && G / S <= kSplitGroups && sp.nblocks >= G / S &&
+             (size_t)G * cdiv(sp.nblocks, G / S) <= W.split_slots;
+    };
+    const int want = env_int(names[j], 0);
+    const int R = want > 0 ? want : rows_s[j], K = want > 0 ? want : k_s[j];
+    if (W.Mp == 128 && row_tiles_on() && groups(R) &&
+        split_rows_fits(cdiv(sp.nblocks, G / R), cdiv(cdiv(sp.nblocks, G / R), R), sp.q4 != 0)) {
+      sp.split = R;
+      sp.split_rows = 1;
+    } else if (steps[j] != STEP_QKV && !sp.q4 && groups(K)) {
+      sp.split = K;
+    }
+  }
+}
+
 int run_pass(const Pass& a, const TreeArgs& tree) {
   const Shape s(*a.cfg);
   const PackedLayout P(s);
@@ -189,59 +257,15 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   p.d_nb = s.d_nb;
   const long long w_off[kSteps] = {(long long)P.w_qkv, (long long)P.w_o, (long long)P.w_gate_up,
                                    (long long)P.w_down, (long long)P.lm_head};
+  plan_steps(s, p.step);
   for (int i = 0; i < kSteps; ++i) {
     StepPlan& sp = p.step[i];
-    sp.nblocks = step_blocks(s, i);
-    sp.layer_rel = i == STEP_LM ? 0 : 1;
-    sp.q4 = s.q4 && i != STEP_LM ? 1 : 0;
-    // bf16: k-steps of 32 inputs; 4-bit: scale groups of 128 inputs
-    sp.ksteps = sp.q4 ? step_groups(s, i) : step_ksteps(s, i);
     sp.w_off = w_off[i];
     sp.s_off = sp.q4 ? w_off[i] + (long long)q4_codes_bytes(sp.nblocks, sp.ksteps) : 0;
-    sp.split = 1;
     sp.wide = i == STEP_GATE_UP && wide ? 1 : 0;
   }
-  // Split-K: groups of S workgroups share a group of column blocks, each over
-  // 1/S of the k-steps, so each reads 1/S of the activations per block of
-  // weights; the partial tiles meet in memory and each workgroup finishes 1/S
-  // of the group's blocks.  The region for the partial tiles runs from the
-  // attention's to the end of split-K's own.
-  p.row_tiles = env_int("LLMCAD_ROW_TILES", 1) == 2 ? 0 : 1;  // (diagnostics: 2 turns the row-split tiles off)
-  const size_t part_room = (W.part - W.attn_o) / ((size_t)W.Mp / 16 * 1024) + W.part_slots;
-  {
-    // At 128 rows a CU's loads bound every step (see split_rows_phase): QKV in
-    // pairs, O and the down projection in fours (7B: 5383 us per pass without
-    // QKV's, 5308 without O's, 5264 with all; the down projection in pairs
-    // 5605, in eights 5422 against 5318 in fours).  Not gate/up, whose groups'
-    // partial tiles are the largest and whose weights alone take two thirds of
-    // the time.
-    // At 64 rows: the down projection in pairs (-3.5% per pass at 41 rows; at
-    // 32 rows, and for O, the hand-off costs more than it saves).
-    // (LLMCAD_SPLIT_QKV / _O / _GU / _DOWN, diagnostics, ask for 1, 2, 4 or 8.)
-    const char* names[4] = {"LLMCAD_SPLIT_QKV", "LLMCAD_SPLIT_O", "LLMCAD_SPLIT_GU", "LLMCAD_SPLIT_DOWN"};
-    // 4-bit steps: O and down in pairs (77 nodes: 4291 us without, 4026 with;
-    // QKV in pairs too 4122, down in fours 4040).
-    const int rows_s[4] = {s.q4 ? 1 : 2, s.q4 ? 2 : 4, 1, s.q4 ? 2 : 4};  // with row-split (or 4-bit) tiles
-    const int k_s[4] = {1, 1, 1, W.Mp >= 64 ? 2 : 1};                     // with K-split tiles
-    for (int j = 0; j < 4; ++j) {
-      StepPlan& sp = p.step[j];
-      // groups of S workgroups with at least a block each, whose partial tiles fit the region
-      auto groups = [&](int S) {
-        return (S == 2 || S == 4 || S == 8) && G % S == 0 && G / S <= kSplitGroups && sp.nblocks >= G / S &&
-               (size_t)G * cdiv(sp.nblocks, G / S) <= part_room;
-      };
-      const int want = env_int(names[j], 0);
-      const int R = want > 0 ? want : rows_s[j], K = want > 0 ? want : k_s[j];
-      if (W.Mp == 128 && p.row_tiles && groups(R) &&
-          split_rows_fits(cdiv(sp.nblocks, G / R), cdiv(cdiv(sp.nblocks, G / R), R), j != STEP_GATE_UP,
-                          sp.q4 != 0)) {
-        sp.split = R;
-        sp.split_rows = 1;
-      } else if ((j == STEP_O || j == STEP_DOWN) && !sp.q4 && K <= kMaxSplitK && groups(K)) {
-        sp.split = K;
-      }
-    }
-  }
+  p.row_tiles = row_tiles_on() ? 1 : 0;
+  plan_split_k(s, W, G, p.step);
   p.k_cache = (bf16*)a.k_cache;
   p.v_cache = (bf16*)a.v_cache;
   p.tree = (int*)(ws + W.tree);
@@ -275,7 +299,7 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
   p.attn_o = (float*)(ws + W.attn_o);
   p.attn_ml = (float*)(ws + W.attn_ml);
   p.head_cnt = (int*)(ws + W.head_counters());
-  p.part = (float*)(ws + W.attn_o);
+  p.part = (float*)(ws + W.split);
   p.grp_cnt = (int*)(ws + W.group_counters());
   p.lm_cnt = (int*)(ws + W.lm_cnt());
   p.exit_cnt = (int*)(ws + W.exit_cnt());
@@ -745,6 +769,24 @@ const char* llmcad_status_string(int status) {
     case LLMCAD_EWORKSPACE: return "workspace or packed image too small";
     default: return "unknown status";
   }
+}
+
+int llmcad_split_plan(const llmcad_config* cfg, int32_t n, int32_t* plan) {
+  const int rc = check_cfg(cfg);
+  if (rc != LLMCAD_OK) return rc;
+  if (!plan || n < 1 || n > kMaxNodes) return LLMCAD_EARG;
+  const Shape s(*cfg);
+  const int G = pass_grid();
+  StepPlan step[kSteps];
+  memset(step, 0, sizeof(step));
+  plan_steps(s, step);
+  plan_split_k(s, WorkspaceLayout(s, n, G), G, step);
+  for (int j = 0; j < STEP_LM; ++j) {
+    plan[3 * j] = step[j].split;
+    plan[3 * j + 1] = step[j].split_rows;
+    plan[3 * j + 2] = cdiv(step[j].nblocks, G / step[j].split);
+  }
+  return LLMCAD_OK;
 }
 
 int llmcad_workspace_region(const llmcad_config* cfg, int32_t max_n, int32_t which, size_t* offset,

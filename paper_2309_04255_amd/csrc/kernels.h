@@ -45,7 +45,7 @@ struct StepPlan {
   long long s_off;      // 4-bit: the packed scales, offset as w_off
   int layer_rel;        // 1 if w_off is relative to the layer's start
   int q4;               // 1: 4-bit codes with group scales
-  int split;            // split-K: workgroups sharing each group of column blocks (1: none; 2, 4 or 8)
+  int split;            // split-K: workgroups sharing each group of column blocks (1: none; 2 or 4)
   int split_rows;       // 1: its split-K runs row-split tiles (128-row passes)
   int wl_cap;           // weight stages per wave copied to LDS before the step's barrier, at most
   int wide;             // 16- and 32-row passes: tiles of up to 9 blocks instead of 8
@@ -96,7 +96,7 @@ struct PassParams {
   float* part;      // split-K partial tiles: per workgroup w, [cdiv(blocks, G/S)][MB] x 1 KiB
                     // (fp32 [64 lanes][4]) from slot w cdiv(blocks, G/S); the attention's partials
                     // share the region (each is written and read within its phase)
-  int* grp_cnt;     // [QKV, O, gate/up, down][kSplitGroups] arrivals of the workgroups of each split-K group
+  int* grp_cnt;     // [step][kSplitGroups] arrivals of the workgroups of each split-K group
   float* lm_val;    // [Mp][G] LM-head argmax per row and workgroup
   int* lm_idx;
   float* lm_sum;    // [Mp][G] sum of exp(logit - the workgroup's max) over its columns (with cand)
@@ -126,9 +126,11 @@ inline int pass_blocks(int n) {
   return mb <= 4 ? mb : mb <= 6 ? 6 : 8;
 }
 hipError_t launch_pass(int mb16, const PassParams& p, const TreeArgs& tree, hipStream_t st);
+// Blocks of the widest K-split tile of that instance.
+int pass_tile_blocks(int mb16);
 // Whether a group of cw blocks, of which a workgroup finishes up to oc, fits one
-// row-split tile of a 128-row pass (epi: the step has epilogue inputs).
-bool split_rows_fits(int cw, int oc, bool epi, bool q4);
+// row-split (or 4-bit) tile of a 128-row pass.
+bool split_rows_fits(int cw, int oc, bool q4);
 int pass_occupancy(int mb16, int dh, bool wide);  // resident workgroups per CU (0 if unavailable)
 
 

@@ -24,7 +24,6 @@ constexpr int kQ4ScaleBytes = kNB * 2;
 constexpr int kMaxNodes = LLMCAD_MAX_NODES;
 constexpr int kAttnMaxSplits = 4;   // key splits per (head, 16-row block)
 constexpr int kMaxSplitK = 4;       // workgroups sharing the k-steps of a group of column blocks
-constexpr int kMaxRowSplit = 8;     // the same at 128 rows with row-split tiles
 constexpr int kPassMaxGrid = 1024;  // workgroups of the pass
 constexpr int kSplitGroups = 256;   // groups of one split-K step, at most
 constexpr int kBarSlots = 16;       // grid-barrier counters
@@ -154,7 +153,7 @@ struct WorkspaceLayout {
   int Mp;
   int n_head_counters;
   int n_group_counters;
-  size_t part_slots;   // 1 KiB x Mp/16 partial tiles the split-K region holds
+  size_t split_slots;  // 1 KiB x Mp/16 partial tiles the split-K region holds
   size_t counters;     // int32: (head, row block) [H][8] | lm | exit | status | split-K groups
   size_t counters_bytes;
   size_t bar;          // int32 [kBarSlots][kBarStride] grid-barrier counters
@@ -175,7 +174,7 @@ struct WorkspaceLayout {
   size_t hs;           // bf16 [L] x (Mp x Fp, fragment order)  SwiGLU product
   size_t attn_o;       // fp32 [H][Mp/16][KS][16][Dh]  key-split partial attention outputs
   size_t attn_ml;      // fp32 [H][Mp/16][KS][16][2]   their running max and sum
-  size_t part;         // fp32 [part_slots][Mp/16][64][4]  split-K partial tiles
+  size_t split;        // fp32 [split_slots][Mp/16][64][4]  split-K partial tiles: over attn_o and attn_ml, and on
   size_t trace;        // int64 [G][4 + 5L][8]    phase timestamps (diagnostics)
   size_t total;
   WorkspaceLayout(const Shape& s, int max_n, int G) {
@@ -191,7 +190,7 @@ struct WorkspaceLayout {
     // that their offsets do not depend on the pass's node count or grid:
     // llmcad_workspace_init clears them once for every later pass.
     n_head_counters = s.H * (kMaxNodes / 16);
-    n_group_counters = 4 * kSplitGroups;  // [QKV, O, gate/up, down][groups]
+    n_group_counters = 4 * kSplitGroups;  // by step: QKV, O, gate/up (never split), down
     counters_bytes = (size_t)(n_head_counters + 4 + n_group_counters) * 4;
     counters = take(counters_bytes);
     bar = take((size_t)kBarSlots * kBarStride * 4);
@@ -212,12 +211,17 @@ struct WorkspaceLayout {
     hs = take((size_t)s.L * Mp * s.Fp * 2);
     attn_o = take((size_t)s.H * Mp * kAttnMaxSplits * s.Dh * 4);
     attn_ml = take((size_t)s.H * Mp * kAttnMaxSplits * 2 * 4);
-    // split-K steps (O, down: d/16 column blocks; passes of 32 or more
-    // rows) in groups of S <= kMaxSplitK workgroups: each workgroup keeps a
-    // partial tile of every block of its group, G cdiv(d/16, G/S) <=
-    // S d/16 + G of them
-    part_slots = Mp >= 32 ? (size_t)kMaxSplitK * s.d_nb + G : 0;
-    part = take(part_slots * (Mp / 16) * 1024);
+    // Split-K steps (passes of 32 or more rows; groups of S workgroups, see
+    // api.hip): each workgroup keeps a partial tile of every block of its
+    // group, G cdiv(blocks, G/S) of them.  A step's partial tiles and the
+    // attention's partials are each written and read within their own phase,
+    // so the region runs from attn_o over attn_ml to the end of one of its own
+    // (the three stay neighbours).  The latter holds O and down (d/16 blocks)
+    // in groups of kMaxSplitK; together they hold QKV in pairs, too.
+    const size_t own_slots = Mp >= 32 ? (size_t)kMaxSplitK * s.d_nb + G : 0;
+    const size_t own = take(own_slots * (Mp / 16) * 1024);
+    split = attn_o;
+    split_slots = (own - split) / ((size_t)(Mp / 16) * 1024) + own_slots;
     trace = take((size_t)G * pass_phases(s.L) * 8 * 8);
     total = o_;
   }

@@ -21,7 +21,7 @@
 // 16-column blocks of a step are dealt out in contiguous runs, one run per
 // workgroup, and every block is computed over the full K by one workgroup,
 // so no partial sum leaves the CU and the epilogue follows the main loop
-// directly (except the split-K projections of 64+ row passes, below).  The
+// directly (except split-K groups, below).  The
 // four waves take interleaved 32-wide k-steps; per k-step a wave loads one
 // 1 KiB weight fragment per block (non-temporal: weights are read once) and
 // one 1 KiB activation fragment per 16-row block -- the activations are
@@ -32,10 +32,11 @@
 // The waves' partial tiles meet in LDS and are added in wave order
 // (bit-reproducible).  Inputs of the epilogue that do not depend on the tile
 // (the residual stream, rotary table, norm gains) are parked in LDS before
-// the barrier.  Passes of 64+ rows add row-split tiles (the waves split the
-// rows and share each weight fragment through LDS) and split-K groups for
-// the projections with one block per workgroup; 4-bit weights have tiles of
-// their own (codes dequantised on the matrix cores).
+// the barrier.  Passes of 33+ rows add row-split tiles (the waves split the
+// rows and share each weight fragment through LDS) and split-K groups: the
+// down projection at 64 rows, O and down and, where its runs are long, QKV at
+// 128; 4-bit weights have tiles of their own (codes dequantised on the matrix
+// cores).
 //
 // Coherence without cache maintenance: every buffer handed from one phase to
 // the next is written once per pass at its own address with device-coherent
@@ -1639,9 +1640,8 @@ __device__ __attribute__((noinline, not_tail_called)) void finish_tile(KParams& 
   __syncthreads();
 }
 
-// ---- split-K (projections with one column block per workgroup at 64 or
-// more rows: every workgroup would read the whole activation matrix per
-// block of weights)
+// ---- split-K (where the activations a workgroup reads per block of weights
+// outweigh the hand-off: the rule is the host's, plan_split_k)
 //
 // Groups of S consecutive workgroups (virtual index) share a group of column
 // blocks; workgroup s of a group computes every block of the group over the
@@ -1790,13 +1790,13 @@ __device__ __forceinline__ bool split_phase(KParams& pin, int step, int layer,
 // issues them and wherever they land: mixed with a stream from HBM, the
 // activations (L2 hits) come at the stream's latency, about 25 bytes per clock
 // and CU for both together, against 52 for L2 hits alone.  What counts at 128
-// rows is then the bytes a CU loads: at the 7B shape QKV 1417 KiB of
-// activations and weights, 953 with S = 2 and the exchange; O 1152, 430 with
-// S = 4; down 3168, 1760 with S = 2, 1100 with S = 4 (loops of 23.6 -> 18.9 us,
-// and 25.5 -> 20.1 us for down in fours instead of pairs).
+// rows is then the bytes a CU loads: at the 7B shape O 1152 KiB of activations
+// and weights, 430 with S = 4; down 3168, 1760 with S = 2, 1100 with S = 4 (a
+// loop of 25.5 us in pairs, 20.1 in fours).  (QKV 1417, 953 with S = 2 and the
+// exchange: a loop of 18.9 instead of 23.6 us, but the exchange costs as much.)
 // 4-bit steps run the same way with their own tiles of up to kSplitTileQ4
 // blocks: their codes are a quarter of the weights, so the activations weigh
-// more (77 nodes, O and down in pairs: 4291 -> 4026 us per pass).
+// more.
 constexpr int kSplitTile = 12, kSplitTileQ4 = 6;
 
 // Adds the other slices' partial tiles (slice t's from src + t stride floats,
@@ -1805,7 +1805,7 @@ constexpr int kSplitTile = 12, kSplitTileQ4 = 6;
 template <int S>
 __device__ __forceinline__ void split_gather(const float* src, size_t stride, int sl, char* own, int units) {
   const int lane = threadIdx.x & 63;
-  constexpr int NB = S == 2 ? 8 : S == 4 ? 4 : 2;
+  constexpr int NB = S == 2 ? 8 : 4;
   for (int u0 = wave_index(); u0 < units; u0 += kWaves * NB) {
     f32x4 o[NB][S - 1];  // the slices other than sl, in order
 #pragma unroll
@@ -1895,10 +1895,8 @@ __device__ __forceinline__ bool split_rows_phase(KParams& pin, int step, int lay
   const float* src = p.part + (size_t)g * S * bstride * U + (size_t)olo * U + lane * 4;
   if (S == 2)
     split_gather<2>(src, (size_t)bstride * U, sl, own, oc * MB);
-  else if (S == 4)
-    split_gather<4>(src, (size_t)bstride * U, sl, own, oc * MB);
   else
-    split_gather<8>(src, (size_t)bstride * U, sl, own, oc * MB);
+    split_gather<4>(src, (size_t)bstride * U, sl, own, oc * MB);
   __syncthreads();
   finish_tile<MB, EPI>(p, step, layer, glo + olo, oc, 1, olo * MB);
   trace_mark(sy, phase, 5);
@@ -2172,8 +2170,8 @@ __device__ __forceinline__ void attn_compute(const AttnStep<DH>& R, const bf16x8
 // two into registers and the next into its share of the LDS, so after the
 // barrier only the queries and the tree's keys (written by the QKV phase) are
 // waited for.  The waves' partial results are merged in LDS, in wave order;
-// with KS > 1 the prefix-only splits store their partial results and the
-// tree's split merges them with its own, in split order.  MB: 16-row blocks
+// with KS > 1 every split stores its partial results and the last to arrive
+// merges them all, in split order.  MB: 16-row blocks
 // of the pass.
 template <int MB, int DH>
 __device__ __attribute__((noinline, not_tail_called)) bool attn_phase(KParams& pin, int layer, int phase) {
@@ -2594,8 +2592,6 @@ __global__ __launch_bounds__(kThreads, 1) void pass_kernel(const PassParams p_ar
       if (!ok || (p.kv_only && l == p.L - 1)) break;
       grid_arrive(sy, phase++);
       ok = attn_phase<LMB, DH>(p, l, phase);
-    } else if (MB > 4 && p.step[STEP_GATE_UP].split_rows) {
-      if constexpr (MB > 4) ok = split_rows_phase<MB, EPI_SWIGLU>(p, STEP_GATE_UP, l, phase);
     } else {
       ok = gemm_phase<MB, EPI_SWIGLU, WIDE ? 9 : 8>(p, STEP_GATE_UP, l, phase);
     }
@@ -2699,8 +2695,10 @@ int pass_occupancy(int mb16, int dh, bool wide) {
 #undef LLMCAD_OCC_CASE
 }
 
-bool split_rows_fits(int cw, int oc, bool epi, bool q4) {
-  return cw <= (q4 ? kSplitTileQ4 : kSplitTile) && (cw - oc) * 8 * 1024 + (epi ? wl_off(oc, 8, 1) : epi_off(oc, 8, 1)) <= kGemmLdsBytes &&
+int pass_tile_blocks(int mb16) { return tile_max_blocks(mb16); }
+
+bool split_rows_fits(int cw, int oc, bool q4) {
+  return cw <= (q4 ? kSplitTileQ4 : kSplitTile) && (cw - oc) * 8 * 1024 + wl_off(oc, 8, 1) <= kGemmLdsBytes &&
          epi_off(cw, 8, 1) <= kGemmLdsBytes;
 }
 

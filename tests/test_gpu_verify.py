@@ -160,9 +160,13 @@ def test_split_k_variants(model, monkeypatch, tree):
     # for a block per group: 64 and 24 workgroups (with 24 and S = 4 some
     # workgroups of a group finish no block).  Each variant meets the oracle
     # bar, and (bf16 models) its logits differ from the unsplit pass's
-    # somewhere (another order of fp32 additions): the split path ran.
+    # somewhere (another order of fp32 additions): the split path ran.  K-split
+    # tiles throughout: at 128 rows the row-split ones, which would come first,
+    # are off.  (4-bit steps have no K-split groups: these passes are unsplit.)
     parent = TREES[tree]
     tok = workloads.draw_tokens(len(parent), model.shape.vocab, seed=11)
+    if len(parent) > 64:
+        monkeypatch.setenv("LLMCAD_ROW_TILES", "2")
     for grid, s_o, s_down in ((64, 4, 4), (64, 2, 4), (24, 4, 2), (24, 2, 4)):
         monkeypatch.setenv("LLMCAD_PASS_GRID", str(grid))
         monkeypatch.setenv("LLMCAD_SPLIT_O", "1")
@@ -170,6 +174,11 @@ def test_split_k_variants(model, monkeypatch, tree):
         base = _check_all(model, parent, tok, f"grid {grid} unsplit")
         monkeypatch.setenv("LLMCAD_SPLIT_O", str(s_o))
         monkeypatch.setenv("LLMCAD_SPLIT_DOWN", str(s_down))
+        # (a step with fewer than a block per group stays unsplit: tiny's 16 blocks on 32 groups)
+        want = [S if model.shape.weight_bits == 16 and model.shape.d_model // 16 >= grid // S else 1
+                for S in (s_o, s_down)]
+        plan = model.binding.split_plan(model.sess.cfg, len(parent))
+        assert (plan["o"][:2], plan["down"][:2]) == ((want[0], False), (want[1], False))
         split = _check_all(model, parent, tok, f"grid {grid} split O {s_o} down {s_down}")
         if model.shape.weight_bits == 16:
             assert not np.array_equal(base, split), "the split-K path did not run"
@@ -203,26 +212,69 @@ def test_row_split_tiles(model, monkeypatch, tree):
         monkeypatch.delenv("LLMCAD_PASS_GRID")
 
 
-@pytest.mark.parametrize("grid,S", [(32, 2), (16, 2), (16, 4), (32, 8), (64, 8), (24, 4)])
-def test_split_k_row_tiles(model, monkeypatch, grid, S):
-    # Split-K with row-split tiles (128-row passes): every step of a layer in
-    # groups of S workgroups, each over a slice of the k-steps (with S = 8 some
-    # of one k-step or none), with groups of 1 to 12 blocks, shares of several
-    # blocks and of none; steps whose groups do not fit run as without it.  The oracle
-    # bar, other sums than the unsplit pass's, and the same bits twice.
-    parent = TREES["random_n128" if grid != 24 else "random_n77"]
-    tok = workloads.draw_tokens(len(parent), model.shape.vocab, seed=17)
+# bf16 and 4-bit shapes of 72 QKV and 24 O and down blocks for split-K groups of
+# 1 to 12 blocks at 128 rows; 12 k-steps (3 scale groups) into QKV and O, 32
+# (11) into down.
+SPLIT_SHAPES = {
+    16: workloads.ModelShape("split", 2, 384, 3, 128, 1000, 998, seed=0x5EED0150),
+    4: workloads.ModelShape("q4split", 2, 384, 3, 128, 1408, 998, seed=0x5EED0151, weight_bits=4),
+}
+# (bits, step, workgroups per group, grid, blocks of the largest group, tree)
+SPLIT_CASES = [
+    (16, "qkv", 2, 48, 3, "random_n128"), (16, "qkv", 2, 28, 6, "random_n77"), (16, "qkv", 2, 20, 8, "random_n128"),
+    (16, "qkv", 2, 16, 9, "random_n77"), (16, "qkv", 2, 14, 11, "random_n128"),
+    (16, "o", 2, 24, 2, "random_n128"), (16, "o", 2, 12, 4, "random_n77"), (16, "o", 4, 96, 1, "random_n128"),
+    (16, "o", 4, 32, 3, "random_n77"), (16, "o", 4, 20, 5, "random_n128"), (16, "o", 4, 12, 8, "random_n77"),
+    (16, "o", 4, 8, 12, "random_n128"), (16, "down", 2, 6, 8, "random_n128"), (16, "down", 4, 96, 1, "random_n77"),
+    (16, "down", 4, 16, 6, "random_n128"), (16, "down", 4, 8, 12, "random_n77"),
+    (4, "qkv", 2, 24, 6, "random_n128"), (4, "o", 2, 48, 1, "random_n128"), (4, "o", 2, 16, 3, "random_n77"),
+    (4, "o", 2, 8, 6, "random_n128"), (4, "o", 4, 32, 3, "random_n77"), (4, "down", 2, 12, 4, "random_n77"),
+    (4, "down", 2, 8, 6, "random_n128"), (4, "down", 4, 20, 5, "random_n77"),
+]
+
+
+@pytest.fixture(scope="module")
+def split_models():
+    binding = _gpu()
+    out = {}
+    for bits, shape in SPLIT_SHAPES.items():
+        gen = workloads.make_weights(shape, "cuda", gain_jitter=0.1)
+        sess = binding.Session(shape, capacity=P + 200, max_n=128)
+        binding.workspace_init(sess.cfg, 128, sess.workspace)
+        sess.load_weights(gen)
+        m = types.SimpleNamespace(shape=shape, sess=sess, ow=oracle_weights(shape, gain_jitter=0.1), binding=binding)
+        prefix = workloads.draw_tokens(P, shape.vocab, seed=3)
+        m.ok, m.ov = oracle.prefill_kv(m.ow, prefix, rounding=True)
+        sess.prefill(prefix, 0)
+        out[bits] = m
+    return out
+
+
+@pytest.mark.parametrize("bits,step,S,grid,blocks,tree", SPLIT_CASES)
+def test_split_k_row_tiles(split_models, monkeypatch, bits, step, S, grid, blocks, tree):
+    # Split-K at 128 rows (row-split or 4-bit tiles): one step at a time in
+    # groups of S workgroups, each over a slice of the k-steps (4-bit O in fours:
+    # one slice of none), with shares of several blocks and of none.  The plan
+    # is the one named, and the pass meets the oracle bar and repeats bit for
+    # bit.  With bf16 weights it differs from the unsplit one somewhere (another
+    # order of sums: the path ran); a 4-bit step of three groups adds three terms
+    # a column, whose order seldom outlives the rounding to bf16.
+    m = split_models[bits]
+    n = len(TREES[tree])
+    tok = workloads.draw_tokens(n, m.shape.vocab, seed=17)
     monkeypatch.setenv("LLMCAD_PASS_GRID", str(grid))
-    names = ("QKV", "O", "GU", "DOWN")
-    for name in names:
+    for name in ("QKV", "O", "DOWN"):
         monkeypatch.setenv(f"LLMCAD_SPLIT_{name}", "1")
-    base = _check_all(model, parent, tok, f"grid {grid} unsplit")
-    for name in names:
-        monkeypatch.setenv(f"LLMCAD_SPLIT_{name}", str(S))
-    split = _check_all(model, parent, tok, f"grid {grid} S {S}")
-    if model.shape.weight_bits == 16:
+    assert all(p[0] == 1 for p in m.binding.split_plan(m.sess.cfg, n).values())
+    base = _check_all(m, TREES[tree], tok, f"{m.shape.name} grid {grid} unsplit")
+    monkeypatch.setenv(f"LLMCAD_SPLIT_{step.upper()}", str(S))
+    for name, p in m.binding.split_plan(m.sess.cfg, n).items():
+        assert p[:2] == ((S, True) if name == step else (1, False))
+        assert name != step or p[2] == blocks
+    split = _check_all(m, TREES[tree], tok, f"{m.shape.name} grid {grid} {step} S {S}")
+    if bits == 16:
         assert not np.array_equal(base, split), "the split-K path did not run"
-    np.testing.assert_array_equal(split, _run(model, parent, tok)[0])
+    np.testing.assert_array_equal(split, _run(m, TREES[tree], tok)[0])
 
 
 def _long_prefix_session(model, PL):
