@@ -349,7 +349,12 @@ const char* llmcad_status_string(int status);
  * RMSNorm that reads it, bf16 [2L+1] x [Mp][d] in fragment order (the input
  * of the QKV, gate/up and LM-head products), 13 the line of zeros that the
  * kernels read in place of absent inputs (cleared by llmcad_workspace_init);
- * Mp = max_n rounded up to 16, 32, 64 or 128, Fp = F rounded up to 32.  Offsets describe a
+ * Mp = max_n rounded up to 16, 32, 64 or 128, Fp = F rounded up to 32.  A pass
+ * that only fills the cache (a prefill chunk whose logits nobody asked for,
+ * llmcad_extend_tree with logits = NULL) ends with the last layer's queries,
+ * keys and values: it leaves 0 and 4, the last layer's part of 10 and 11 (2
+ * and 3 of a one-layer model) and the last two versions of 7, 8 and 12 as they
+ * were.  Offsets describe a
  * pass over max_n nodes (call with max_n = that pass's n); those of regions 5
  * and 13, which hold state from one pass to the next, depend on neither the
  * node count nor the pass's grid. */
