@@ -344,6 +344,18 @@ int run_pass(const Pass& a, const TreeArgs& tree) {
 // device (scratch_base) and only that address is handed to the kernels.
 static __device__ __align__(256) char scratch[LLMCAD_SCRATCH_BYTES];
 
+__global__ __launch_bounds__(256) void clear_kernel(float4* p, unsigned pieces) {
+  const unsigned i = blockIdx.x * 256 + threadIdx.x;
+  if (i < pieces) p[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+}
+
+// Zeros, p 16-byte aligned, bytes a multiple of 16.
+hipError_t launch_clear(void* p, size_t bytes, hipStream_t st) {
+  const unsigned pieces = (unsigned)(bytes / 16);
+  clear_kernel<<<dim3((pieces + 255) / 256), dim3(256), 0, st>>>((float4*)p, pieces);
+  return hipGetLastError();
+}
+
 // Device address of this device's `scratch` (null if the lookup failed; the
 // HIP status is kept for llmcad_status_string).
 char* scratch_base() {
@@ -545,7 +557,9 @@ int llmcad_verify_tree_noalloc(const llmcad_config* cfg, const void* packed, voi
   // The scratch keeps the previous call's contents: its synchronisation
   // state (counters with the pass status, barrier counters, the zero line,
   // which lie first and together) starts every call cleared.
-  HIP_TRY(hipMemsetAsync(ws, 0, W.zero + kZeroBytes, st));
+  // (By a kernel: the call may be captured, and memset nodes of a graph have
+  // given wrong results on replays after the first.)
+  HIP_TRY(launch_clear(ws, W.zero + kZeroBytes, st));
   Pass a;
   a.cfg = cfg;
   a.packed = (const char*)packed;

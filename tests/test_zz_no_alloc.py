@@ -78,3 +78,39 @@ def test_noalloc_rejects_passes_beyond_its_scratch(model):
                                      sess.logits, sess.path, sess.accept_len, sess.next_token,
                                      raise_on_error=False)
     assert rc == binding.EWORKSPACE
+
+
+def test_noalloc_in_a_graph(model):
+    # Captured once and replayed, with passes of its own and synchronisations in
+    # between and outputs spoilt before each: every replay gives the eager
+    # call's bits and ends with status 0 (the scratch's counters start cleared
+    # every time).
+    shape, sess, binding = model
+    parent = workloads.complete_tree((2, 2, 2, 2))
+    n = len(parent)
+    tok = workloads.draw_tokens(n, shape.vocab, seed=50)
+    status = torch.full((1,), -7, dtype=torch.int32, device=sess.device)
+
+    def call():
+        binding.verify_tree_noalloc(sess.cfg, sess.packed, sess.k_cache, sess.v_cache, P, tok, parent, sess.logits,
+                                    sess.path, sess.accept_len, sess.next_token, status)
+
+    call()
+    torch.cuda.synchronize()
+    want = _outputs(sess, n)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    other = workloads.complete_tree((2, 2, 2))
+    for replay in range(4):
+        for t in (sess.logits, sess.path, sess.accept_len, sess.next_token, status):
+            t.fill_(-7)
+        if replay % 2:  # (the scratch then holds another pass's state)
+            binding.verify_tree_noalloc(sess.cfg, sess.packed, sess.k_cache, sess.v_cache, P, tok[:len(other)], other,
+                                        sess.logits, sess.path, sess.accept_len, sess.next_token)
+            torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(status.item()) == binding.PASS_OK
+        for g, w, what in zip(_outputs(sess, n), want, ("logits", "path", "accept_len", "next_token")):
+            assert torch.equal(g, w), f"{shape.name} replay {replay}: {what} differs"
