@@ -453,7 +453,10 @@ __device__ __forceinline__ void chunk_sums(const f32x4 (&sr)[N]) {
 // wave's sums come between its first loads and its first product).
 __host__ __device__ constexpr bool scales_before_loop(int MB) { return MB == 1; }
 
-// Widest K-split tile (a gate/up step marked wide: 9 at 16 and 32 rows).
+// Widest K-split tile (a gate/up step marked wide: 9 at 16 and 32 rows).  8 at 3
+// row blocks: 13B at 41 nodes (gate/up runs of 7) 6400 us per pass against 6520
+// with 6, which sends longer runs to row-split tiles; 7B (runs of 6, the LM head
+// of 8) 3970 / 3958, 1B 1347 / 1328.
 __host__ __device__ constexpr int tile_max_blocks(int MB) {
   return MB <= 3 ? 8 : MB == 4 ? LLMCAD_TILE_BLOCKS_MB4 : LLMCAD_TILE_BLOCKS_MB8;
 }
@@ -909,11 +912,13 @@ constexpr int q4_tile_blocks() {
 // accumulate on top of it: sum_k (q_k - 8) a_k in fp32, which the column's
 // scale then multiplies into the accumulator -- w = s (q - 8) is never formed.
 //
-// A layer's codes are a quarter of the bf16 bytes, so most of a tile fits the
-// LDS: before the barrier waves 1-3 copy there the codes and scales of as
-// many groups as the region holds (the partial-tile slots' room too: they are
-// written only after the loop) and load the next D into registers, so that
-// after the barrier little but the activations is waited for.  At the 7B shape
+// A layer's codes are a quarter of the bf16 bytes, so most of a tile of a
+// residual step (O, down) fits the LDS: before the barrier waves 1-3 copy there
+// the codes and scales of as many groups as the region holds (the partial-tile
+// slots' room too: they are written only after the loop) and load the next D
+// into registers, so that after the barrier little but the activations is
+// waited for.  QKV and gate/up load all theirs through registers.  At the 7B
+// shape
 // QKV / O / gate-up / down loops take 6.8 / 3.3 / 9.5 / 7.8 us at 31 nodes and
 // 20 / 12 / 28 / 30 at 77 (7.5 / 4.7 / 11.4 / 12.6, and, with tiles of one
 // block that read the activations once per block, 56 / 13 / 93 / 35, when all
