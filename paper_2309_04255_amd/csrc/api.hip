@@ -181,7 +181,9 @@ bool row_tiles_on() { return env_int("LLMCAD_ROW_TILES", 1) != 2; }
 //   4717, 4592).
 // At 64 rows the down projection in pairs, with K-split tiles (3 row blocks: 3968
 // against 4027 at 7B after 2048 positions, 6276 / 6557 at 13B; 4 row blocks: 3811
-// / 3955 at 7B), and not O (within 0.3%).  At 32 rows neither (7B).
+// / 3955 at 7B), and not O (within 0.3%).  At 32 rows neither: 7B loses 0.5 to 4%
+// by either, 1B and 30B 1 to 5% by O and nothing by down (within 0.6%); only 13B
+// would gain, by down in pairs (5729 against 5939 at 31 nodes).
 // (LLMCAD_SPLIT_QKV / _O / _DOWN, diagnostics, ask for 1, 2 or 4.)
 void plan_split_k(const Shape& s, const WorkspaceLayout& W, int G, StepPlan* step) {
   const int steps[3] = {STEP_QKV, STEP_O, STEP_DOWN};

@@ -918,11 +918,10 @@ constexpr int q4_tile_blocks() {
 // slots' room too: they are written only after the loop) and load the next D
 // into registers, so that after the barrier little but the activations is
 // waited for.  QKV and gate/up load all theirs through registers.  At the 7B
-// shape
-// QKV / O / gate-up / down loops take 6.8 / 3.3 / 9.5 / 7.8 us at 31 nodes and
-// 20 / 12 / 28 / 30 at 77 (7.5 / 4.7 / 11.4 / 12.6, and, with tiles of one
-// block that read the activations once per block, 56 / 13 / 93 / 35, when all
-// codes came through registers and each wave kept every row block).
+// shape QKV / O / gate-up / down loops take 6.7 / 3.2 / 9.3 / 7.4 us at 31 nodes
+// (7.5 / 4.7 / 11.4 / 12.6 when all codes came through registers) and 15 / 5.6 /
+// 22 / 14 at 77 (56 / 13 / 93 / 35 with every row block kept by each wave: tiles
+// of one block, which read the activations once per block).
 template <int MB, int C>
 __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KParams& pin, int step, int layer,
                                                                           int nb0, int wait_phase, int k0, int kn,
