@@ -113,7 +113,7 @@ def write_traffic(fetch_csv, write_csv, workload, copy_mib):
     wl = workloads.get_workload(workload)
     n = len(workloads.make_tree(wl.tree, wl.shape.vocab, wl.seed)[0])
     mb = -(-n // 16)
-    mb = 1 if mb <= 1 else 2 if mb <= 2 else 4 if mb <= 4 else 8
+    mb = mb if mb <= 4 else 6 if mb <= 6 else 8
     inst = re.compile(rf"pass_kernel<{mb}, {wl.shape.head_dim}(, (true|false))?>")
     names = [k for k in fetch if inst.search(k)]
     if len(names) != 1:
