@@ -420,17 +420,24 @@ __device__ __forceinline__ void epilogue_inputs(KParams& p, const TileIn& io, in
 
 // RMSNorm scale of a row, 1 / sqrt(mean of squares + eps), 0 for rows >= n,
 // from its chunk sums in GemmLds::part_ss ([64 / MB][16 MB]), added in chunk
-// order.  (The additions are a chain of 64 / MB.  A tree over the workgroup is
-// shorter but rounds otherwise, and where a model's two best tokens are closer
+// order by one thread.  (A chain of 64 / MB additions.  A tree over the workgroup
+// is shorter but rounds otherwise, and where a model's two best tokens are closer
 // than bf16 resolves the greedy tokens follow the rounding: a 30B pass over 8
-// nodes then takes another path.)
+// nodes then takes another path.  All sums are loaded before the first addition:
+// left to itself the compiler keeps one or two LDS loads in flight, and a 1B
+// draft step takes 1173 us, a 7B pass over 13 nodes 2991; this way 1152 and 2974,
+// with the tree 1145 and 2973.  Added before the main loop by the last wave:
+// 1142, but 2996, and 3267 against 3227 for 7B at 31 nodes.)
 template <int MB>
 __device__ __forceinline__ float row_scale(KParams& p, int row) {
   GemmLds& gl = gemm_lds();
   constexpr int ROWS = 16 * MB, CHK = 4 * kThreads / ROWS;
-  float t = 0.0f;
+  float v[CHK], t = 0.0f;
 #pragma unroll
-  for (int c = 0; c < CHK; ++c) t += gl.part_ss[c * ROWS + row];
+  for (int c = 0; c < CHK; ++c) v[c] = gl.part_ss[c * ROWS + row];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int c = 0; c < CHK; ++c) t += v[c];
   return row < p.n ? 1.0f / sqrtf(t * p.inv_d + p.eps) : 0.0f;
 }
 
@@ -445,13 +452,6 @@ __device__ __forceinline__ void chunk_sums(const f32x4 (&sr)[N]) {
   for (int k = 1; k < N; ++k) t += sr[k];
   *(f32x4*)&gemm_lds().part_ss[ch * 16 * MB + 4 * q] = t;
 }
-
-// Where a pass of 16 or 32 rows adds them up: at 16 rows before the main loop,
-// by the last wave, its chain of 64 behind the other waves' loads (1B draft
-// step 1157 us per pass, 1173 with the chain in the epilogue); at 32 rows in the
-// epilogue (7B, 31 nodes: 3227 us per pass, 3267 before the loop, where every
-// wave's sums come between its first loads and its first product).
-__host__ __device__ constexpr bool scales_before_loop(int MB) { return MB == 1; }
 
 // Widest K-split tile (a gate/up step marked wide: 9 at 16 and 32 rows).  8 at 3
 // row blocks: 13B at 41 nodes (gate/up runs of 7) 6400 us per pass against 6520
@@ -598,16 +598,10 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
   // count them exactly), and wave 0's LDS stages, copied by wave 1, are
   // visible to it.  Then wave 0's register stages.
   __builtin_amdgcn_s_waitcnt(0);
-  if constexpr (scales_before_loop(MB)) {
-    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
-  }
   lds_barrier();
   if (wave == 0) {
 #pragma unroll
     for (int u = 0; u < D; ++u) load_w(u, P + u, true);
-  }
-  if constexpr (scales_before_loop(MB)) {
-    if (wave == kWaves - 1 && io.norm && p.ssq_regs && lane < 16 * MB) gemm_lds().rstd[lane] = row_scale<MB>(p, lane);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0 && p.trace != nullptr && threadIdx.x == 0)
@@ -664,7 +658,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute(KParams&
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (SSQR && !scales_before_loop(MB)) {
+  if constexpr (SSQR) {
     if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
   }
   // This wave's partial tile -> LDS; the epilogue adds the four in wave
@@ -1042,16 +1036,10 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
 #pragma unroll
   for (int u = 0; u < D; ++u) load_a(u, u);
   __builtin_amdgcn_s_waitcnt(0);
-  if constexpr (scales_before_loop(MB)) {
-    if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
-  }
   lds_barrier();
   if (wave == 0) {
 #pragma unroll
     for (int u = 0; u < D; ++u) load_w(u, P + u);
-  }
-  if constexpr (scales_before_loop(MB)) {
-    if (wave == kWaves - 1 && io.norm && p.ssq_regs && lane < 16 * MB) gemm_lds().rstd[lane] = row_scale<MB>(p, lane);
   }
   __builtin_amdgcn_sched_barrier(0);
   if (wait_phase >= 0 && p.trace != nullptr && threadIdx.x == 0)
@@ -1137,7 +1125,7 @@ __device__ __attribute__((noinline, not_tail_called)) bool tile_compute_q4(KPara
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (SSQR && !scales_before_loop(MB)) {
+  if constexpr (SSQR) {
     if (io.norm && p.ssq_regs) chunk_sums<MB>(sr);
   }
   lds_barrier();  // (the slots' room may hold codes another wave still reads)
@@ -1205,12 +1193,12 @@ __device__ __forceinline__ void row_rstd(KParams& p, const float* ssq) {
 }
 
 // A norm step's row scales, into gl.rstd.  When its tile held the sums of squares
-// in registers they are there already, or their chunk sums are.
+// in registers their chunk sums are in gl.part_ss already.
 template <int MB>
 __device__ __forceinline__ void row_scales(KParams& p, const StepIo& io) {
   if (MB > 2 || !p.ssq_regs) {
     row_rstd<layout_mb(MB)>(p, io.ssq);
-  } else if constexpr (!scales_before_loop(MB)) {
+  } else {
     if (threadIdx.x < 16 * MB) gemm_lds().rstd[threadIdx.x] = row_scale<MB>(p, threadIdx.x);
     __syncthreads();
   }
